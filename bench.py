@@ -397,29 +397,46 @@ def ln_partials_on(H):
     return {"0": False, "1": True}.get(env, H <= 6144)
 
 
+def mfma_rows(rows, K, g, ln, cus):
+    """Row tiles per workgroup of the matrix-core GEMV (the library's rule)."""
+    rt, kt = -(-rows // 16), -(-K // 32)
+    load = lambda r: -(-(-(-rt // r) * g) // cus) * r
+    even = rt * g % cus == 0
+    if g > 1:
+        return 5 if load(5) <= load(1) and (ln or not even or kt // g >= 128) else 1
+    if even and not ln:
+        return 2 if rt % (2 * cus) == 0 and rt <= 4 * cus else 1
+    if load(3) <= min(load(1), load(2)):
+        return 3
+    return 2 if load(2) <= load(1) else 1
+
+
 def gemv_label(B, H, F, dt, tiled, partials=True, cus=256):
     """GEMV kernels an all-resident eager step at batch B runs (the library's dispatch rules;
     tiled: the step runs the tile-ordered copy of the weights; partials: with LayerNorm
-    partials between its matrix-core linears; cus: the device's compute units)."""
+    partials between its matrix-core linears; cus: the device's compute units).  The matrix-core
+    kernel is named with the batch, the k-tiles per request and, above 1, the row tiles per
+    workgroup."""
     t = "BF16" if dt == 1 else "F16"
     if tiled:
         parts = {}
         for name, (n, k) in zip(NAMES, shapes(H, F)):
             g = mfma_splits(n, k, cus)
-            wgs = -(-n // 16) * g
-            kmajor = wgs % cus == 0 and wgs // cus <= 4  # the library's tile order rule
-            split = ("" if g == 1 else " (K split %d)" % g) + (" k-major" if kmajor else "")
-            u = 4 if g > 1 else 8  # tiles per request, no LayerNorm
-            if partials and name in ("qkv", "fc1"):
-                uln = 8 if (g == 1 and B == 1 and -(-wgs // cus) <= 3) else 4  # with the LayerNorm prologue
-                key = "gemv_mfma_kernel<%s,%d,%d,LayerNorm from partials>%s" % (t, B, uln, split)
-                parts.setdefault(key, []).append("qkv after layer 0" if name == "qkv" else name)
-                if name == "qkv":
-                    key = "gemv_mfma_kernel<%s,%d,%d>%s" % (t, B, u, split)
-                    parts.setdefault(key, []).append("layer 0's qkv")
-                continue
-            key = "gemv_mfma_kernel<%s,%d,%d>%s" % (t, B, u, split)
-            parts.setdefault(key, []).append(name)
+            rt = -(-n // 16)
+            kmajor = rt * g % cus == 0 and rt * g // cus <= 3  # the library's tile order rule
+
+            def add(ln, what):
+                r = mfma_rows(n, k, g, ln, cus)
+                u = 8 if r == 1 and g == 1 and (not ln or rt <= cus or k > 4096) else 4
+                key = "gemv_mfma_kernel<%s,%d,%d%s%s>%s%s" % (
+                    t, B, u, ",%d row tiles" % r if r > 1 else "", ",LayerNorm from partials" if ln else "",
+                    "" if g == 1 else " (K split %d)" % g, " k-major" if kmajor else "")
+                parts.setdefault(key, []).append(what)
+            if partials and name == "qkv":
+                add(True, "qkv after layer 0")
+                add(False, "layer 0's qkv")
+            else:
+                add(partials and name == "fc1", name)
         ni = -(-H // 2048)
         ni = ni if ni <= 5 else 8
         return " + ".join("%s: %s" % (k, ", ".join(v)) for k, v in parts.items()) + \

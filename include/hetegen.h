@@ -355,7 +355,7 @@ HETEGEN_API hetegen_status hetegen_module_schedule(const double* t_cpu, const do
  * LayerNorm launch (Chan-Golub-LeVeque combination in a fixed order), when H <= 6144:
  * for larger hidden sizes combining the H / 16 partials costs more than the launch (the
  * variable HETEGEN_LN_PARTIALS=0 or 1 at creation forces the launches or the partials).
- * A tiled linear whose matrix-core grid puts the same number of workgroups, 1 to 4, on
+ * A tiled linear whose matrix-core grid puts the same number of workgroups, 1 to 3, on
  * every compute unit keeps its tiles k-major (k-tile kt of row tile rt at tile kt *
  * ceil(n_gpu / 16) + rt), so that workgroups walking K side by side read one contiguous
  * window; the others keep hetegen_tile_weights' order (HETEGEN_TILE_KORDER=0 or 1 at

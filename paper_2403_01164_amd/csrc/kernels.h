@@ -135,7 +135,7 @@ hipError_t launch_tile(const void* W, long long ldw, int rows, int K, void* dst,
 // and the workspace a launch at batch B needs (0 when not split).
 int mfma_splits(int rows, int K);
 // Tile order for a model's copy of W [rows, K] on the current device: 1 k-major, 0 row-tile
-// order (1 when the launch grid puts the same number of workgroups, at most 4, on every CU).
+// order (1 when the launch grid puts the same number of workgroups, at most 3, on every CU).
 int mfma_kmajor(int rows, int K);
 size_t mfma_ws_floats(int rows, int K, int B);
 size_t mfma_cnt_words(int rows, int K);

@@ -680,20 +680,28 @@ __global__ __launch_bounds__(kThreads) void gemv_ln1_kernel(GemvParams p) {
 // B <= 8 activation rows with N weight rows; v_mfma_f32_16x16x32 takes one 1 KiB tile
 // of 16 weight rows x 32 columns as its 16-row operand (one 16-byte load per lane,
 // the whole tile in one coalesced instruction) and the matching 32 columns of x as its
-// 16-column operand (batch row b in lanes b, b + 16, b + 32, b + 48; the columns past
-// B repeat row B - 1 and their results are dropped).  The products and their fp32 sums
-// happen in the matrix core, so no lane reduction is needed and the instruction cost
-// per weight byte does not grow with B: the kernel stays bound by HBM at every batch
-// size, where the vector GEMV becomes bound by its dot products and LDS reads of x.
+// 16-column operand.  The products and their fp32 sums happen in the matrix core, so no
+// lane reduction is needed and the instruction cost per weight byte does not grow with B:
+// the kernel stays bound by HBM at every batch size, where the vector GEMV becomes bound by
+// its dot products and LDS reads of x.
 //
-// Workgroup (row tile rt, split g) of 4 wavefronts takes k-tiles of split g of the
-// 16 rows; wavefront w a contiguous quarter of them, U tiles per step with the next
-// step's loads in flight.  The four 16x16 partial tiles are summed in LDS in wavefront
+// What it costs beyond the weights is x: B rows of it, read by every workgroup from L2
+// through the same load pipeline.  One load fetches the fragments of two k-tiles (see the
+// kernel), and a workgroup may hold R row tiles that share them (mfma_rows).  Against one
+// fragment load per weight tile (B = 8, us): [4096, 16384] 24.1 -> 22.6, [4096, 4096] 8.8
+// -> 7.9, with the LayerNorm [12288, 4096] 19.4 -> 18.3 and [15360, 5120] 30.1 -> 27.0, and
+// [9216, 36864] 120 -> 105 (6.5 TB/s).
+//
+// Workgroup (R row tiles, split g) of 4 wavefronts takes the k-tiles of split g of its
+// rows, dealt to the wavefronts in chunks of 4 (so the workgroup walks one window of K: with
+// a contiguous quarter per wavefront [4096, 16384] took 24.0 us), U tiles per step with
+// the next step's loads in flight.  The four partial tiles are summed in LDS in wavefront
 // order.  With G > 1 splits, each workgroup stores its partial (coherent stores to
 // memory: the splits run on different XCDs with their own L2) and the last of the G to
 // arrive (an arrival counter, no waiting) adds the G partials in split order, so the
 // result does not depend on timing.  Column order inside a tile is free (both
-// operands use the same one), so every lane's x fragment is 16 contiguous bytes.
+// operands use the same one), so every lane's x fragment is 16 contiguous bytes.  Which
+// tiles are added in which order depends on K and G only: not on B, U or R.
 //
 // LayerNorm without a launch of its own (LN = true): the linear that produced x (out or
 // fc2, this kernel with ln_out) left per-16-row partials of its output; the consumer
@@ -746,11 +754,14 @@ __device__ __forceinline__ uint4 normalize8_fma(const uint4& v, float a, float c
 }
 
 constexpr int kTileRows = 16, kTileK = 32;
+constexpr int kChunkTiles = 4;  // k-tiles dealt to a wavefront at a time
 // K-split choice of the matrix-core GEMV (mfma_splits)
 constexpr double kMaxUneven = 1.15;  // busiest CU's workgroups over the mean, tolerated unsplit
 constexpr int kMaxSplits = 8, kMinSplitTiles = 32;
 constexpr int kMaxDevices = 64, kDefaultCus = 256;
-constexpr int kMaxKmajorPerCu = 4;  // mfma_kmajor
+constexpr int kMaxKmajorPerCu = 3;  // mfma_kmajor
+constexpr int kLongSplitTiles = 128;  // mfma_rows
+constexpr int kLongLnK = 4096;        // launch_mfma_t
 constexpr int kLnGroup = 16;    // elements per LayerNorm partial
 constexpr int kLnSlots = 8;     // batch rows per partial group (the largest batch)
 constexpr int kLnMaxGroups = kMaxLnK / kLnGroup;
@@ -763,52 +774,67 @@ constexpr int kLnMaxGroups = kMaxLnK / kLnGroup;
 // group holds both rows' pairs): lane l takes groups l + 64 i in increasing i, and the
 // lanes are combined in a fixed DPP tree, so every workgroup gets the same bits with no
 // reduction across wavefronts; one barrier publishes the statistics.
-constexpr int kLnGroupsPerLane = kLnMaxGroups / 64;
+constexpr int kLnRegGroups = 6;  // groups per lane kept in registers: K <= 6144, the widths that use partials by default
 
-template <int B>
-__device__ __forceinline__ void ln_partials_load(const float* __restrict__ pt, int K,
-                                                 f32x4 (&v)[kLnGroupsPerLane]) {
+// Group i of this lane for wavefront w's rows: a lane past the last group of a round rereads
+// it (the reduction drops it); slot 2w + 1 past B holds nothing the launch uses.
+__device__ __forceinline__ f32x4 ln_partial(const float* __restrict__ pt, int QG, int i) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int QG = (K + kLnGroup - 1) / kLnGroup, rounds = (QG + 63) / 64;  // the same for the workgroup
-  if (2 * wave >= B) return;
-  // a lane past the last group of a round rereads it (the reduction drops it); slot 2w + 1
-  // past B holds nothing this launch uses
-#pragma unroll
-  for (int i = 0; i < kLnGroupsPerLane; ++i)
-    if (i < rounds) {
-      const int q = min(lane + 64 * i, QG - 1);
-      v[i] = *gmem((const f32x4*)(pt + ((size_t)q * kLnSlots + 2 * wave) * 2));
-    }
+  const int q = min(lane + 64 * i, QG - 1);
+  return *gmem((const f32x4*)(pt + ((size_t)q * kLnSlots + 2 * wave) * 2));
 }
 
-template <int B>
-__device__ __forceinline__ void ln_partials_reduce(const f32x4 (&v)[kLnGroupsPerLane], int K,
-                                                   float (*st)[2]) {
+__device__ __forceinline__ void ln_partials_load(const float* __restrict__ pt, int K, int B,
+                                                 f32x4 (&v)[kLnRegGroups]) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int QG = (K + kLnGroup - 1) / kLnGroup, rounds = (QG + 63) / 64;  // the same for the workgroup
+  if (2 * wave >= B || rounds > kLnRegGroups) return;
+#pragma unroll
+  for (int i = 0; i < kLnRegGroups; ++i)
+    if (i < rounds) v[i] = ln_partial(pt, QG, i);
+}
+
+__device__ __forceinline__ void ln_partials_reduce(const float* __restrict__ pt, const f32x4 (&v)[kLnRegGroups], int K,
+                                                   int B, float (*st)[2]) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int QG = (K + kLnGroup - 1) / kLnGroup, rounds = (QG + 63) / 64;
   if (2 * wave < B) {
     const float inv_k = 1.0f / (float)K;
-    float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-    for (int i = 0; i < kLnGroupsPerLane; ++i)
-      if (i < rounds && lane + 64 * i < QG) {
-        s0 += v[i].x;
-        s1 += v[i].z;
+    float s0 = 0.f, s1 = 0.f, m0 = 0.f, m1 = 0.f, t0 = 0.f, t1 = 0.f;
+    auto add = [&](int i, const f32x4& g) {
+      if (lane + 64 * i < QG) {
+        s0 += g.x;
+        s1 += g.z;
       }
-    const float m0 = wave_sum(s0) * inv_k, m1 = wave_sum(s1) * inv_k;
-    float t0 = 0.f, t1 = 0.f;
-#pragma unroll
-    for (int i = 0; i < kLnGroupsPerLane; ++i) {
+    };
+    auto dev = [&](int i, const f32x4& g) {
       const int q = lane + 64 * i;
-      if (i < rounds && q < QG) {
+      if (q < QG) {
         // a group holds 16 elements, or 8 (the last one when K % 16 == 8; K % 8 == 0): its
         // mean is its sum times an exact power-of-two reciprocal
         const bool full = K - kLnGroup * q >= kLnGroup;
         const float n = full ? (float)kLnGroup : 8.f, inv_n = full ? 1.f / kLnGroup : 0.125f;
-        const float d0 = v[i].x * inv_n - m0, d1 = v[i].z * inv_n - m1;
-        t0 += v[i].y + n * d0 * d0;
-        t1 += v[i].w + n * d1 * d1;
+        const float d0 = g.x * inv_n - m0, d1 = g.z * inv_n - m1;
+        t0 += g.y + n * d0 * d0;
+        t1 += g.w + n * d1 * d1;
       }
+    };
+    const bool regs = rounds <= kLnRegGroups;
+    if (regs) {
+#pragma unroll
+      for (int i = 0; i < kLnRegGroups; ++i)
+        if (i < rounds) add(i, v[i]);
+    } else {  // wider rows: both passes read the partials from the cache
+      for (int i = 0; i < rounds; ++i) add(i, ln_partial(pt, QG, i));
+    }
+    m0 = wave_sum(s0) * inv_k;
+    m1 = wave_sum(s1) * inv_k;
+    if (regs) {
+#pragma unroll
+      for (int i = 0; i < kLnRegGroups; ++i)
+        if (i < rounds) dev(i, v[i]);
+    } else {
+      for (int i = 0; i < rounds; ++i) dev(i, ln_partial(pt, QG, i));
     }
     t0 = wave_sum(t0);
     t1 = wave_sum(t1);
@@ -824,9 +850,11 @@ __device__ __forceinline__ void ln_partials_reduce(const f32x4 (&v)[kLnGroupsPer
   __syncthreads();
 }
 
-template <class T, int B, int U, bool LN>
-__global__ __launch_bounds__(kThreads) void gemv_mfma_kernel(GemvParams p, int G) {
-  __shared__ float part[kWaves][4][64];
+template <class T, int U, int R, bool LN>
+__global__ __launch_bounds__(kThreads) void gemv_mfma_kernel(GemvParams p, int B, int G) {
+  static_assert(U % kChunkTiles == 0, "a request holds whole chunks");
+  constexpr int NQ = (R + 1) / 2;  // outputs per thread: 2 row tiles of 16 rows x 8 batch rows at a time
+  __shared__ float part[kWaves][R][4][64];
   __shared__ float lnst[kLnSlots][2];  // LN: mean and 1 / sqrt(var + eps) of each batch row
   __shared__ int last;
   // the wavefront index through a scalar register: every tile bound below is then
@@ -834,72 +862,136 @@ __global__ __launch_bounds__(kThreads) void gemv_mfma_kernel(GemvParams p, int G
   // compiler cannot prove uniform becomes an execution mask, which matrix-core
   // instructions do not obey (they would run for every skipped tile).
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int K = p.K, KT = (K + kTileK - 1) / kTileK;
-  const int rt = blockIdx.x / G, gi = blockIdx.x - rt * G;
+  const int K = p.K, KT = (K + kTileK - 1) / kTileK, RT = (p.rows + kTileRows - 1) / kTileRows;
+  const int rg = blockIdx.x / G, gi = blockIdx.x - rg * G, rt0 = rg * R;
   const int kg = (KT + G - 1) / G;
   const int kb = min(KT, gi * kg), ke = min(KT, kb + kg);
-  const int pw = (ke - kb + kWaves - 1) / kWaves;
-  const int k0 = min(ke, kb + wave * pw), k1 = min(ke, k0 + pw);
-  const int nst = (k1 - k0 + U - 1) / U;
+  // this wavefront's chunks: c = 0, 1, ... at k-tiles k0 + c * kWaves * kChunkTiles
+  const int k0 = kb + wave * kChunkTiles;
+  constexpr int kStep = kWaves * kChunkTiles;
+  const int nst = ke > k0 ? ((ke - k0 + kStep - 1) / kStep * kChunkTiles + U - 1) / U : 0;
+  auto ktile = [&](int st, int u) { return k0 + (st * (U / kChunkTiles) + u / kChunkTiles) * kStep + u % kChunkTiles; };
   // k-tile kt of row tile rt: tile rt * KT + kt (row-tile order) or kt * RT + rt (k-major)
-  const size_t RT = (size_t)((p.rows + kTileRows - 1) / kTileRows);
-  const uint4* wp = (const uint4*)p.W + (p.korder ? (size_t)rt : (size_t)rt * KT) * 64 + lane;
-  const size_t kstride = p.korder ? RT * 64 : 64;
-  const int b = min(lane & 15, B - 1), grp = lane >> 4;
-  // x fragments through a buffer descriptor over rows [0, B) of x: a lane whose result
-  // column is past B (its products are never read), a group past K and the repeated tile
-  // of a step past k1 get an offset past the descriptor's size, for which the load
-  // returns zeros without a memory access; at B = 8 that halves the x fragments' share of
-  // the load pipeline, and no branch is needed (a branch around the loads makes the
-  // compiler wait for the weights in flight)
+  const size_t kstride = p.korder ? (size_t)RT * 64 : 64, rstride = p.korder ? 64 : (size_t)KT * 64;
+  const uint4* wp[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) wp[r] = (const uint4*)p.W + min(rt0 + r, RT - 1) * rstride + lane;
+  // x fragments, two k-tiles per load: the 16 columns of a product are batch rows 0..7 of
+  // the even k-tile of the pair and batch rows 0..7 of the odd one, so the lanes of a row of
+  // 16 that would hold nothing for B <= 8 fetch the next k-tile's x instead.  The even
+  // tile's product is read from columns 0..7 of its accumulator, the odd tile's from columns
+  // 8..15 of another one; the other halves multiply the wrong x and are dropped.  x goes
+  // through a buffer descriptor over rows [0, B) of x: a lane whose batch row is past B, a
+  // group past K and the tiles past the split's end get an offset past the descriptor's
+  // size, for which the load returns zeros without a memory access and without a branch
+  // (a branch around the loads makes the compiler wait for the weights in flight)
+  const int half = (lane >> 3) & 1, grp = lane >> 4, b = min(lane & 7, B - 1);
   const auto xrs = rsrc(p.x, (uint32_t)(((long long)(B - 1) * p.ldx + K) * 2));
-  const bool xlane = (lane & 15) < B;
+  const bool xlane = (lane & 7) < B;
   const uint32_t xrow = (uint32_t)((long long)b * p.ldx * 2);
+  const uint32_t xlast = xrow + 2u * (half * kTileK + 8 * grp);
+  const uint32_t xfull = xlane ? xlast : kXPast;
   struct Buf {
-    uint4 w[U], x[U];
+    uint4 w[R][U], x[U / 2];
   };
+  // Step st < nst - 1 holds whole chunks only; the last one (and, with the LayerNorm, the
+  // unconditional first one) may run past ke: its tiles past ke reread tile ke - 1 and are
+  // not multiplied.
   auto load = [&](int st, Buf& f) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int kt = min(k0 + st * U + u, k1 - 1);
-      f.w[u] = load_stream(wp + (size_t)kt * kstride);
-      const int kx = kt * kTileK + 8 * grp;  // K % 8 == 0: a group is wholly inside or past K
-      const bool in = xlane & (kx < K) & (k0 + st * U + u < k1);  // no short circuit: no branch
-      const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(xrs, in ? xrow + 2u * kx : kXPast, 0, 0);
-      f.x[u] = make_uint4(v.x, v.y, v.z, v.w);
+      const int kt = ktile(st, u);
+#pragma unroll
+      for (int r = 0; r < R; ++r) f.w[r][u] = load_stream(wp[r] + kt * kstride);
+      if (u % 2 == 0) {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(xrs, xfull, kt * (kTileK * 2), 0);
+        f.x[u / 2] = make_uint4(v.x, v.y, v.z, v.w);
+      }
+    }
+  };
+  auto load_last = [&](int st, Buf& f) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int kt = ktile(st, u), ktc = min(kt, ke - 1);
+#pragma unroll
+      for (int r = 0; r < R; ++r) f.w[r][u] = load_stream(wp[r] + ktc * kstride);
+      if (u % 2 == 0) {
+        // K % 8 == 0: a group of 8 columns is wholly inside or past K
+        const bool in = xlane & ((kt + half) * kTileK + 8 * grp < K) & (kt + half < ke);  // no short circuit: no branch
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(xrs, in ? xlast + 2u * kt * kTileK : kXPast, 0, 0);
+        f.x[u / 2] = make_uint4(v.x, v.y, v.z, v.w);
+      }
     }
   };
   // LayerNorm of x on the fly: xn = x * ln_a + ln_c for this lane's batch row
   float ln_a = 0.f, ln_c = 0.f;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  auto compute = [&](int st, const Buf& f) {
+  f32x4 acc[R][2];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int kt = k0 + st * U + u;
-      if (kt < k1) {
-        uint4 xv = f.x[u];
-        if (LN) {
-          xv = normalize8_fma<T>(xv, ln_a, ln_c);
-          // columns past K (only in the last k-tile when K % 32 != 0) multiply zeros
-          if ((K & (kTileK - 1)) && kt == KT - 1 && kt * kTileK + 8 * grp >= K) xv = make_uint4(0u, 0u, 0u, 0u);
-        }
-        acc = Mma<T>::run(f.w[u], xv, acc);
+  for (int r = 0; r < R; ++r) acc[r][0] = acc[r][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto compute = [&](const Buf& f) {
+#pragma unroll
+    for (int u = 0; u < U; u += 2) {
+      const uint4 xv = LN ? normalize8_fma<T>(f.x[u / 2], ln_a, ln_c) : f.x[u / 2];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        acc[r][0] = Mma<T>::run(f.w[r][u], xv, acc[r][0]);
+        acc[r][1] = Mma<T>::run(f.w[r][u + 1], xv, acc[r][1]);
       }
+    }
+  };
+  auto compute_last = [&](int st, const Buf& f) {
+#pragma unroll
+    for (int u = 0; u < U; u += 2) {
+      const int kt = ktile(st, u);
+      uint4 xv = f.x[u / 2];
+      if (LN) {
+        xv = normalize8_fma<T>(xv, ln_a, ln_c);
+        // columns past K (only in the last k-tile when K % 32 != 0) multiply zeros
+        if ((K & (kTileK - 1)) && (kt + half) * kTileK + 8 * grp >= K) xv = make_uint4(0u, 0u, 0u, 0u);
+      }
+      if (kt < ke) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r][0] = Mma<T>::run(f.w[r][u], xv, acc[r][0]);
+      }
+      if (kt + 1 < ke) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r][1] = Mma<T>::run(f.w[r][u + 1], xv, acc[r][1]);
+      }
+    }
+  };
+  // thread t finishes row i of row tiles rt0 + r0 + 2 q, q < NQ, for batch row j; its bias and
+  // residual are requested ahead of the products (in the epilogue they would cost one more
+  // memory round trip)
+  const int t = threadIdx.x, i = t & 15, j = (t >> 4) & 7, r0 = t >> 7;
+  const int row0 = (rt0 + r0) * kTileRows + i;
+  auto mine = [&](int q) { return j < B && r0 + 2 * q < R; };
+  auto valid = [&](int q) { return mine(q) && row0 + 2 * kTileRows * q < p.rows; };
+  uint16_t bias_v[NQ], resid_v[NQ];
+  auto load_epi = [&] {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int row = row0 + 2 * kTileRows * q;
+      bias_v[q] = resid_v[q] = 0;
+      if (valid(q) && p.bias) bias_v[q] = gmem((const uint16_t*)p.bias)[row];
+      if (valid(q) && p.epi == EPI_RESID) resid_v[q] = gmem((const uint16_t*)p.resid)[j * p.ldr + row];
     }
   };
   Buf fa, fb;
   // the LayerNorm partials are requested before the first weights, so that waiting for
   // them leaves the weight loads in flight
-  f32x4 lnv[LN ? kLnGroupsPerLane : 1];
+  f32x4 lnv[LN ? kLnRegGroups : 1];
   if constexpr (LN) {
-    ln_partials_load<B>(p.ln_in, K, lnv);
+    ln_partials_load(p.ln_in, K, B, lnv);
     __builtin_amdgcn_sched_barrier(0);  // keep them ahead of the weight loads
+  } else {
+    load_epi();
   }
   // (with the LayerNorm the first loads are unconditional, for the same reason; a
-  // wavefront without tiles rereads tile k1 - 1 >= 0 and computes nothing)
-  if (LN || nst > 0) load(0, fa);
+  // wavefront without tiles rereads tile ke - 1 >= 0 and computes nothing)
+  if (LN || nst > 0) load_last(0, fa);
   if constexpr (LN) {
-    ln_partials_reduce<B>(lnv, K, lnst);
+    load_epi();  // after the first weights: waiting for the partials does not wait for these
+    ln_partials_reduce(p.ln_in, lnv, K, B, lnst);
     ln_a = lnst[b][1];
     ln_c = -lnst[b][0] * lnst[b][1];
     if (p.h_out && blockIdx.x == 0) {
@@ -913,69 +1005,110 @@ __global__ __launch_bounds__(kThreads) void gemv_mfma_kernel(GemvParams p, int G
       }
     }
   }
+  // a step's loads stay ahead of the products of the step before (the scheduler would move
+  // the normalisation of arrived fragments above them and let the memory pipe run dry)
+  auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
   int st = 0;
-  for (; st + 2 < nst; st += 2) {
+  for (; st + 3 < nst; st += 2) {
     load(st + 1, fb);
-    compute(st, fa);
+    fence();
+    compute(fa);
+    fence();
     load(st + 2, fa);
-    compute(st + 1, fb);
+    fence();
+    compute(fb);
+    fence();
   }
-  if (st + 1 < nst) {
+  if (st + 2 < nst) {
     load(st + 1, fb);
-    compute(st, fa);
-    compute(st + 1, fb);
+    fence();
+    compute(fa);
+    load_last(st + 2, fa);
+    fence();
+    compute(fb);
+    fence();
+    compute_last(st + 2, fa);
+  } else if (st + 1 < nst) {
+    load_last(st + 1, fb);
+    fence();
+    compute(fa);
+    fence();
+    compute_last(st + 1, fb);
   } else if (st < nst) {
-    compute(st, fa);
+    compute_last(st, fa);
   }
-  // lane l of the result holds rows 4 (l / 16) + v, v < 4, of column l % 16
+  // lane l of an accumulator holds rows 4 (l / 16) + v, v < 4, of column l % 16: the even
+  // tiles' sum of batch row j is in column j, the odd tiles' in column j + 8 (rotated by 8
+  // lanes within its row of 16)
 #pragma unroll
-  for (int v = 0; v < 4; ++v) part[wave][v][lane] = acc[v];
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float odd = acc[r][1][v];
+      part[wave][r][v][lane] = acc[r][0][v] + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+                                                                            0, __builtin_bit_cast(int, odd), 0x128, 0xF,
+                                                                            0xF, false));  // row_ror:8
+    }
   __syncthreads();
-  const int t = threadIdx.x, i = t & 15, j = t >> 4;  // row i of the tile, batch row j
-  const bool mine = t < 16 * B;
   const int l = j + 16 * (i >> 2), v = i & 3;
-  float s = 0.f;
-  if (mine) s = (part[0][v][l] + part[1][v][l]) + (part[2][v][l] + part[3][v][l]);
+  float s[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int r = min(r0 + 2 * q, R - 1);
+    s[q] = (part[0][r][v][l] + part[1][r][v][l]) + (part[2][r][v][l] + part[3][r][v][l]);
+  }
   if (G > 1) {
-    const uint32_t pbytes = (uint32_t)(G * 16 * B * sizeof(float));
-    const auto rs = rsrc(p.ws + (size_t)rt * G * 16 * B, pbytes);
-    if (mine)
-      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, s), rs, (gi * 16 * B + t) * 4, 0,
-                                            kCoherent);
-    __builtin_amdgcn_s_waitcnt(0);  // this thread's partial store has completed
+    const int nr = min(R, RT - rt0), one = kTileRows * B;  // floats of one row tile's partial
+    const auto rs = rsrc(p.ws + (size_t)rt0 * G * one, (uint32_t)(nr * G * one * (int)sizeof(float)));
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+      if (mine(q) && r0 + 2 * q < nr)
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, s[q]), rs,
+                                              (((r0 + 2 * q) * G + gi) * one + j * kTileRows + i) * 4, 0, kCoherent);
+    __builtin_amdgcn_s_waitcnt(0);  // this thread's partial stores have completed
     __syncthreads();
     if (t == 0) {
-      const uint32_t prev = __hip_atomic_fetch_add(p.cnt + rt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint32_t prev = __hip_atomic_fetch_add(p.cnt + rg, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       last = prev == (uint32_t)(G - 1);
-      if (last) __hip_atomic_store(p.cnt + rt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next launch
+      if (last) __hip_atomic_store(p.cnt + rg, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next launch
     }
     __syncthreads();
     if (!last) return;
-    if (mine) {
-      s = 0.f;
-      for (int q = 0; q < G; ++q)
-        s += __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (q * 16 * B + t) * 4, 0, kCoherent));
+    // the partials are requested together (one round trip) and added in split order; a split
+    // past G reads past the descriptor's size or another tile's partial and is not added
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      float pv[kMaxSplits];
+#pragma unroll
+      for (int g = 0; g < kMaxSplits; ++g)
+        pv[g] = __builtin_bit_cast(
+            float, __builtin_amdgcn_raw_buffer_load_b32(
+                       rs, mine(q) && g < G ? (uint32_t)(((r0 + 2 * q) * G + g) * one + j * kTileRows + i) * 4u : kXPast,
+                       0, kCoherent));
+      s[q] = pv[0];
+#pragma unroll
+      for (int g = 1; g < kMaxSplits; ++g)
+        if (g < G) s[q] += pv[g];
     }
   }
-  const int row = rt * kTileRows + i;
-  const bool valid = mine && row < p.rows;
-  float yv = 0.f;
-  if (valid) {
-    const uint16_t* bias = (const uint16_t*)p.bias;
-    const float y = s + (bias ? T::to_f32(bias[row]) : 0.f);
-    const float rv = p.epi == EPI_RESID ? T::to_f32(((const uint16_t*)p.resid)[j * p.ldr + row]) : 0.f;
-    yv = apply_epi(y, p.epi, rv);
-    store_y<T>(p.y, j * p.ldy + row, p.y_f32, yv);
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int rt = rt0 + r0 + 2 * q, row = row0 + 2 * kTileRows * q;
+    float yv = 0.f;
+    if (valid(q)) {
+      yv = apply_epi(s[q] + T::to_f32(bias_v[q]), p.epi, T::to_f32(resid_v[q]));
+      store_y<T>(p.y, j * p.ldy + row, p.y_f32, yv);
+    }
+    // LayerNorm partials of this row tile's outputs for the next linear: a row of 16 lanes
+    // holds the 16 rows of one batch row
+    if (!p.ln_out) continue;
+    const float n = (float)min(kTileRows, p.rows - rt * kTileRows);
+    const float a = valid(q) ? T::to_f32(round_act<T>(yv)) : 0.f;
+    const float s1 = row16_sum(a);
+    const float d = valid(q) ? a - s1 / n : 0.f;
+    const float m2 = row16_sum(d * d);
+    if (valid(q) && i == 0) *(f32x2*)(p.ln_out + ((size_t)rt * kLnSlots + j) * 2) = f32x2{s1, m2};
   }
-  // LayerNorm partials of this row tile's outputs for the next linear: a row of 16
-  // lanes holds the 16 rows of one batch row (lanes past 16 B hold none)
-  if (!p.ln_out || wave * 64 >= 16 * B) return;
-  const float n = (float)min(kTileRows, p.rows - rt * kTileRows);
-  const float a = valid ? T::to_f32(round_act<T>(yv)) : 0.f;
-  const float s1 = row16_sum(a);
-  const float d = valid ? a - s1 / n : 0.f;
-  const float m2 = row16_sum(d * d);
-  if (mine && i == 0) *(f32x2*)(p.ln_out + ((size_t)rt * kLnSlots + j) * 2) = f32x2{s1, m2};
 }
 
 // Tile order of W [rows, K]: one 16-byte group per thread (see tiled_bytes in kernels.h).
@@ -1594,13 +1727,14 @@ int mfma_splits(int rows, int K) {
   return best;
 }
 
-// k-major tiles when the grid puts the same number of workgroups, 1 to 4, on every CU: all
-// of them then start together and walk K side by side, and in row-tile order their loads
-// would fall on the same offsets of blocks a fixed multiple of 16 rows apart, crowding a few
-// memory channels (OPT-6.7B fc2 [4096, 16384] at B = 8: 23.9 against 25.5 us in a decode
-// step, and the whole step 2.42 against 2.49 ms); k-major, the walk reads one contiguous
-// window.  With more workgroups per CU, or uneven ones, they drift apart and k-major
-// scatters the loads instead (OPT-30B fc1 [28672, 7168], 7 per CU: 72.8 against 70.5 us).
+// k-major tiles when the row tiles and splits put the same number of workgroups, 1 to 3, on
+// every CU: all of them then start together and walk K side by side, and in row-tile order
+// their loads would fall on the same offsets of blocks a fixed multiple of 16 rows apart,
+// crowding a few memory channels (B = 8, row-tile order / k-major: OPT-6.7B fc2 [4096, 16384]
+// 24.2 / 22.8 us, out [4096, 4096] 8.6 / 8.0, qkv [12288, 4096] 19.1 / 18.2); k-major, the
+// walk reads one contiguous window.  With more workgroups per CU, or uneven ones, they drift
+// apart and k-major scatters the loads instead (OPT-6.7B fc1 [16384, 4096], 4 per CU: 22.6 /
+// 23.5 us; OPT-30B fc1 [28672, 7168], 7 per CU: 70.5 / 72.8).
 int mfma_kmajor(int rows, int K) {
   if (rows <= 0 || K <= 0) return 0;
   const long long wgs = (long long)((rows + kTileRows - 1) / kTileRows) * mfma_splits(rows, K);
@@ -1619,45 +1753,51 @@ size_t mfma_cnt_words(int rows, int K) {
   return (size_t)((rows + kTileRows - 1) / kTileRows);
 }
 
-// Tiles per request: 4 in split launches and with the LayerNorm prologue (fewer registers)
-// from B = 2 on or when the grid puts more than 3 workgroups on a CU (142-146 VGPRs with 8
-// allow 3 wavefronts per SIMD); 8 otherwise.  Measured on OPT-6.7B shapes: fc2 [4096,
-// 16384] took 4 while every lane of the product loaded x (24.6 against 23.9 us at B = 8),
-// and 8 since lanes of columns past B load none (whole steps 2.354-2.357 against
-// 2.383-2.385 ms at B = 8; OPT-30B fc2 [7168, 28672] unchanged); qkv with the prologue at
-// B = 8 with 8: 2.370-2.374 against 2.356-2.357 ms per step; at B = 1 on tiles (a model
-// without the row-major copy), 8 for every unsplit linear but fc1 (4 workgroups per CU):
-// 2.260-2.265 against 2.279-2.282 ms.  Each wavefront sums its k-tiles in order either way:
-// the bits are the same.
-template <class T, int B, bool LN>
-hipError_t launch_mfma_ln(const GemvParams& p, int G, hipStream_t s) {
-  const int grid = ((p.rows + kTileRows - 1) / kTileRows) * G;
-  const int cus = device_cus();
-  const bool u4 = G > 1 || (LN && (B > 1 || (grid + cus - 1) / cus > 3));
-  if (u4) hipLaunchKernelGGL((gemv_mfma_kernel<T, B, 4, LN>), dim3(grid), dim3(kThreads), 0, s, p, G);
-  else if (LN) hipLaunchKernelGGL((gemv_mfma_kernel<T, 1, 8, true>), dim3(grid), dim3(kThreads), 0, s, p, 1);
-  else hipLaunchKernelGGL((gemv_mfma_kernel<T, B, 8, false>), dim3(grid), dim3(kThreads), 0, s, p, 1);
+// Row tiles per workgroup.  More of them share the x fragments (and the LayerNorm prologue
+// and normalisation) of a k-tile, but make the grid coarser: what a CU then reads is
+// ceil(workgroups / CUs) * R row tiles, and R is taken only where that is no more than with
+// one row tile per workgroup.  Unsplit: the largest such R up to 3; where one row tile per
+// workgroup already loads the CUs evenly and there is no LayerNorm, only 2 for grids of 2
+// or 4 per CU ([8192, 4096] 15.1 -> 12.5 us, [16384, 4096] 23.2 -> 22.9; none of 3, 6 or 8).  Split: 5 or 1 (5
+// brings the OPT-66B grids, 1152 workgroups, to 232, all running at once), 5 only with the
+// LayerNorm, on an uneven grid or for long splits: the merge of 5 row tiles costs more than
+// of one.  Measured at B = 8 (us, R = 1 / 2 / 3 / 5): [15360, 5120] with the LayerNorm 29.0
+// / 27.0 / 33.6 / 30.1, [16384, 4096] with it 25.2 / 23.5 / 27.8 / 25.0, [7168, 28672] 70.2
+// / 65.2 / 79.4 / 115, [21504, 7168] 51.7 / 51.0 / 50.2 / 70.5, [28672, 7168] 64.1 / 67.8 /
+// 72.3 / 79.7; split [9216, 36864] in 2 115 / 120 / 120 / 105, [5120, 20480] in 4 39.6 /
+// 39.8 / 38.8 / 38.2, [5120, 5120] in 4 14.1 / 15.7 / 13.9 / 14.5.  R does not change the bits.
+int mfma_rows(int rows, int K, int G, bool ln) {
+  const int KT = (K + kTileK - 1) / kTileK, RT = (rows + kTileRows - 1) / kTileRows, cus = device_cus();
+  auto load = [&](int r) { return ((long long)(RT + r - 1) / r * G + cus - 1) / cus * r; };
+  const bool even = (long long)RT * G % cus == 0;
+  if (G > 1) return load(5) <= load(1) && (ln || !even || KT / G >= kLongSplitTiles) ? 5 : 1;
+  if (even && !ln) return RT % (2 * cus) == 0 && RT <= 4 * cus ? 2 : 1;
+  if (load(3) <= std::min(load(1), load(2))) return 3;
+  return load(2) <= load(1) ? 2 : 1;
+}
+
+template <class T, int U, int R, bool LN>
+hipError_t launch_mfma_k(const GemvParams& p, int B, int G, hipStream_t s) {
+  const int RT = (p.rows + kTileRows - 1) / kTileRows;
+  hipLaunchKernelGGL((gemv_mfma_kernel<T, U, R, LN>), dim3((RT + R - 1) / R * G), dim3(kThreads), 0, s, p, B, G);
   return hipGetLastError();
 }
 
-template <class T, int B>
-hipError_t launch_mfma_b(const GemvParams& p, int G, hipStream_t s) {
-  return p.ln ? launch_mfma_ln<T, B, true>(p, G, s) : launch_mfma_ln<T, B, false>(p, G, s);
-}
-
-template <class T>
+// k-tiles per request and row tile: 4 when a workgroup holds several row tiles and in split
+// launches (more requests in flight gained nothing there), 8 otherwise; with the LayerNorm
+// and one row tile 8 only where registers are not short, i.e. at most one workgroup per CU
+// ([4096, 1024] 4.55 against 5.05 us with 4: its whole K is one request) or rows long enough
+// to pay for it ([20480, 5120] 36.2 against 37.0, but [12288, 4096] 18.7 against 18.4).
+template <class T, bool LN>
 hipError_t launch_mfma_t(const GemvParams& p, int B, int G, hipStream_t s) {
-  switch (B) {
-    case 1: return launch_mfma_b<T, 1>(p, G, s);
-    case 2: return launch_mfma_b<T, 2>(p, G, s);
-    case 3: return launch_mfma_b<T, 3>(p, G, s);
-    case 4: return launch_mfma_b<T, 4>(p, G, s);
-    case 5: return launch_mfma_b<T, 5>(p, G, s);
-    case 6: return launch_mfma_b<T, 6>(p, G, s);
-    case 7: return launch_mfma_b<T, 7>(p, G, s);
-    case 8: return launch_mfma_b<T, 8>(p, G, s);
+  const int RT = (p.rows + kTileRows - 1) / kTileRows;
+  switch (mfma_rows(p.rows, p.K, G, LN)) {
+    case 5: return launch_mfma_k<T, 4, 5, LN>(p, B, G, s);
+    case 3: return launch_mfma_k<T, 4, 3, LN>(p, B, G, s);
+    case 2: return launch_mfma_k<T, 4, 2, LN>(p, B, G, s);
   }
-  return hipErrorInvalidValue;
+  const bool u8 = G == 1 && (!LN || RT <= device_cus() || p.K > kLongLnK);
+  return u8 ? launch_mfma_k<T, 8, 1, LN>(p, B, G, s) : launch_mfma_k<T, 4, 1, LN>(p, B, G, s);
 }
 
 size_t ln_partials_floats(int n) { return n > 0 ? (size_t)((n + kLnGroup - 1) / kLnGroup) * kLnSlots * 2 : 0; }
@@ -1672,7 +1812,8 @@ hipError_t launch_gemv_mfma(GemvParams p, int dtype, int B, hipStream_t stream) 
   if (G > 1 && (!p.ws || !p.cnt || p.ws_floats < mfma_ws_floats(p.rows, p.K, B) ||
                 p.cnt_words < mfma_cnt_words(p.rows, p.K)))
     return hipErrorInvalidValue;
-  return dtype == 1 ? launch_mfma_t<BF16>(p, B, G, stream) : launch_mfma_t<F16>(p, B, G, stream);
+  if (p.ln) return dtype == 1 ? launch_mfma_t<BF16, true>(p, B, G, stream) : launch_mfma_t<F16, true>(p, B, G, stream);
+  return dtype == 1 ? launch_mfma_t<BF16, false>(p, B, G, stream) : launch_mfma_t<F16, false>(p, B, G, stream);
 }
 
 }  // namespace hg
