@@ -39,4 +39,16 @@ int attn_max_positions();
 // dtype: 0 = fp16, 1 = bf16; head_dim 64 or 128.
 hipError_t launch_attention(AttnParams a, int dtype, int B, hipStream_t stream);
 
+// Positions [pos0, pos0 + n) of one layer's cache (kc, vc as in AttnParams) and token-major
+// device buffers k, v [B, n, heads * head_dim] in the model's 16-bit type; all pointers
+// 16-byte aligned.  to_cache: buffers -> cache, else cache -> buffers.
+struct KvCopyParams {
+  void* kc;
+  void* vc;
+  void* k;
+  void* v;
+  int heads, head_dim, max_seq, pos0, n;
+};
+hipError_t launch_kv_copy(const KvCopyParams& a, int B, bool to_cache, hipStream_t stream);
+
 }  // namespace hg
