@@ -624,6 +624,7 @@ struct Job {
   int segmajor;     // W_dev segment-major (resident row-major copy, batch 1)
   const float* ln_in;  // tiled, ln, all rows resident: LayerNorm from these partials of x
   float* ln_out;       // tiled, all rows resident: also write the partials of y here
+  bool rows_mfma;      // resident row-major rows may run on the matrix cores (hg::gemv_rows_wanted)
 };
 
 hetegen_status run_gemv(hetegen_ctx* ctx, const Job& j, const void* x, long long ldx, int ln, const void* W, int row0,
@@ -656,6 +657,8 @@ hetegen_status run_gemv(hetegen_ctx* ctx, const Job& j, const void* x, long long
     p.ln_in = ln ? j.ln_in : nullptr;
     p.ln_out = j.ln_out;
     HIPCHK(ctx, hg::launch_gemv_mfma(p, j.dtype, j.B, st));
+  } else if (resident && j.rows_mfma && hg::gemv_rows_wanted(rows, j.K, ldx, j.B)) {
+    HIPCHK(ctx, hg::launch_gemv_rows(p, j.dtype, j.B, st));
   } else {
     HIPCHK(ctx, hg::launch_gemv(p, j.dtype, j.B, st, 0));
   }
@@ -990,6 +993,7 @@ hetegen_status hetegen_linear(hetegen_ctx* ctx, const void* x_dev, int B, int K,
     j.ldy = N;
     j.y_f32 = y_dtype == HETEGEN_F32;
     j.epi = hg::EPI_NONE;
+    j.rows_mfma = true;
     if (!W_dev_resident && n_gpu > 0) {
       if (!pipeline_idle(ctx)) return fail(ctx, HETEGEN_ERR_INVALID_ARG, "internal: stale chunk plan");
       if (pageable) TRY(ensure_pin_resources(ctx));

@@ -761,6 +761,10 @@ constexpr int kMaxSplits = 8, kMinSplitTiles = 32;
 constexpr int kMaxDevices = 64, kDefaultCus = 256;
 constexpr int kMaxKmajorPerCu = 3;  // mfma_kmajor
 constexpr int kLongSplitTiles = 128;  // mfma_rows
+// gemv_rows_wanted, rows_by_8
+constexpr int kRowsFew = 1024, kRowsMany = 16384;
+constexpr int kRowsMinK8 = 1024, kRowsLongK = 8192;
+constexpr double kRowsUneven = 1.2;
 constexpr int kLongLnK = 4096;        // launch_mfma_t
 constexpr int kLnGroup = 16;    // elements per LayerNorm partial
 constexpr int kLnSlots = 8;     // batch rows per partial group (the largest batch)
@@ -1108,6 +1112,162 @@ __global__ __launch_bounds__(kThreads) void gemv_mfma_kernel(GemvParams p, int B
     const float d = valid(q) ? a - s1 / n : 0.f;
     const float m2 = row16_sum(d * d);
     if (valid(q) && i == 0) *(f32x2*)(p.ln_out + ((size_t)rt * kLnSlots + j) * 2) = f32x2{s1, m2};
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Matrix-core GEMV on row-major weights (hetegen_linear's resident rows, see
+// gemv_rows_wanted; no LayerNorm).  Read in the operand's order, a row-major weight would cost
+// half-line loads (64 bytes of each of 16 rows per load); instead a wavefront loads 512 or
+// 1024 contiguous bytes of each of its H = 16 or 8 rows, turns them into operands through
+// its own slice of LDS (rows 16 bytes apart modulo the banks; no workgroup barrier) and
+// multiplies them as gemv_mfma_kernel does, x fragments of two k-tiles per load.
+//  * H = 16: the two k-tiles of a fragment are two products, as in gemv_mfma_kernel.
+//  * H = 8: one product takes both: operand rows 0..7 are the 8 rows at the first k-tile,
+//    rows 8..15 the same rows at the second, so the first tile's sums are in rows 0..7 of
+//    columns 0..7 and the second's in rows 8..15 of columns 8..15.  Twice the workgroups for
+//    the same rows, for grids that would not fill the device; x is then read as often as W.
+// A workgroup owns H rows; its 4 wavefronts take steps of SC columns in turn and are summed
+// in LDS in order, so a row's bits depend on K and H alone.
+// Bound by HBM from a few thousand rows on: [16384, 4096] at B = 8 25.0 us (5.4 TB/s) against
+// 31.8 us on the vector GEMV, [36864, 9216] 101 (6.7 TB/s) against 159; [4096, 4096] 8.6 / 13.0.
+// 8 wavefronts per workgroup, two row tiles per wavefront and wavefronts starting at
+// different columns were slower nearly everywhere.
+// ---------------------------------------------------------------------------
+template <class T, int H>
+__global__ __launch_bounds__(kThreads) void gemv_rows_kernel(GemvParams p, int B) {
+  constexpr int SC = 4096 / H;           // columns per step: 8 KiB of weights per wavefront
+  constexpr int LPR = SC / 8;            // lanes per row of a load
+  constexpr int NL = 8, RPL = 64 / LPR;  // loads per step, rows per load
+  constexpr int NP = SC / 64;            // x fragments (pairs of k-tiles) per step
+  constexpr int PAIR = H == 16 ? 1 : 2;  // k-tiles between the two of a pair (2: other LDS banks)
+  constexpr int kRow = SC * 2 + 16;      // bytes of a row in LDS
+  __shared__ __align__(16) char tile[kWaves][H * kRow];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int K = p.K, row0 = blockIdx.x * H;
+  const int steps = (K + SC - 1) / SC;
+  const int nst = steps > wave ? (steps - wave + kWaves - 1) / kWaves : 0;  // this wavefront's steps wave + 4 st
+  const int col = (lane % LPR) * 8;
+  const uint16_t* wp[NL];
+#pragma unroll
+  for (int i = 0; i < NL; ++i)
+    wp[i] = (const uint16_t*)p.W + (long long)min(row0 + RPL * i + lane / LPR, p.rows - 1) * K + col;
+  const int half = (lane >> 3) & 1, grp = lane >> 4;
+  const auto xrs = rsrc(p.x, (uint32_t)(((long long)(B - 1) * p.ldx + K) * 2));
+  const bool xlane = (lane & 7) < B;
+  const int xcol = half * PAIR * kTileK + 8 * grp;
+  const uint32_t xoff = (uint32_t)((long long)min(lane & 7, B - 1) * p.ldx * 2) + 2u * xcol;
+  // first k-tile of pair u: 2 u, or the pairs (0, 2), (1, 3) of every four
+  auto first = [](int u) { return PAIR == 1 ? 2 * u : (u >> 1) * 4 + (u & 1); };
+  struct Buf {
+    uint4 w[NL], x[NP];
+  };
+  auto load = [&](int st, Buf& f) {
+    const int k0 = (wave + st * kWaves) * SC;
+    // past the row's end (K % 8 == 0: a group of 8 columns is wholly inside or past K): the
+    // row's last group, zeroed below, for the row may hold infinities there
+    const int off = k0 + col < K ? k0 : K - 8 - col;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) f.w[i] = load_stream((const uint4*)(wp[i] + off));
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      const int kx = k0 + first(u) * kTileK;
+      const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(
+          xrs, (xlane & (kx + xcol < K)) ? xoff + 2u * kx : kXPast, 0, 0);
+      f.x[u] = make_uint4(v.x, v.y, v.z, v.w);
+    }
+  };
+  // A wavefront's sum over K in two levels: chains of 4 products, then the sums of two steps.
+  // In one chain its rounding error against 64 bits was 1.7 times the vector GEMV's (64 lanes'
+  // partials) at K = 5128
+  constexpr int NH = H == 16 ? 2 : 1;  // the k-tiles of a pair: two products, or one for both
+  constexpr int NA = NP / 2;           // accumulators per product
+  f32x4 acc[NH][NA], sum[NH];
+  auto clear = [&] {
+#pragma unroll
+    for (int h = 0; h < NH; ++h)
+#pragma unroll
+      for (int n = 0; n < NA; ++n) acc[h][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  auto fold = [&] {
+#pragma unroll
+    for (int h = 0; h < NH; ++h) sum[h] += NA == 4 ? (acc[h][0] + acc[h][1]) + (acc[h][2 % NA] + acc[h][3 % NA])
+                                                   : acc[h][0] + acc[h][1];
+  };
+#pragma unroll
+  for (int h = 0; h < NH; ++h) sum[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+  clear();
+  char* my = tile[wave];
+  auto compute = [&](int st, const Buf& f) {
+    const bool in = (wave + st * kWaves) * SC + col < K;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      uint4 v = f.w[i];
+      if (!in) v = make_uint4(0u, 0u, 0u, 0u);
+      *(uint4*)(my + (RPL * i + lane / LPR) * kRow + col * 2) = v;
+    }
+    // the lanes of a wavefront exchange the rows: LDS serves a wavefront in order, so only
+    // the compiler has to keep the reads behind the writes (and the next step's writes behind)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const char* op = my + (lane & (H - 1)) * kRow + grp * 16 + (H == 8 ? half * PAIR * 64 : 0);
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      acc[0][u % NA] = Mma<T>::run(*(const uint4*)(op + first(u) * 64), f.x[u], acc[0][u % NA]);
+      if constexpr (H == 16)
+        acc[NH - 1][u % NA] = Mma<T>::run(*(const uint4*)(op + first(u) * 64 + 64), f.x[u], acc[NH - 1][u % NA]);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  // thread t finishes row i of batch row j; its bias and residual are requested first
+  const int t = threadIdx.x, i = t % H, j = t / H;
+  const bool valid = j < B && row0 + i < p.rows;
+  uint16_t bias_v = 0, resid_v = 0;
+  if (valid && p.bias) bias_v = gmem((const uint16_t*)p.bias)[row0 + i];
+  if (valid && p.epi == EPI_RESID) resid_v = gmem((const uint16_t*)p.resid)[j * p.ldr + row0 + i];
+  Buf fa, fb;
+  auto fence = [] { __builtin_amdgcn_sched_barrier(0); };  // the loads stay ahead of the products
+  if (nst > 0) load(0, fa);
+  int st = 0;
+  for (; st + 2 < nst; st += 2) {
+    load(st + 1, fb);
+    fence();
+    compute(st, fa);
+    fence();
+    load(st + 2, fa);
+    fence();
+    compute(st + 1, fb);
+    fold();
+    clear();
+    fence();
+  }
+  if (st + 1 < nst) {
+    load(st + 1, fb);
+    fence();
+    compute(st, fa);
+    compute(st + 1, fb);
+  } else if (st < nst) {
+    compute(st, fa);
+  }
+  fold();
+  // the wavefronts' partial tiles through LDS (over the staging rows: a barrier first).  Lane
+  // l holds rows 4 (l / 16) + v of column l % 16; the second tiles' sums are 8 columns on
+  float(*part)[2][4][64] = (float(*)[2][4][64])tile;
+  __syncthreads();
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    part[wave][0][v][lane] = sum[0][v];
+    if constexpr (H == 16) part[wave][1][v][lane] = sum[NH - 1][v];
+  }
+  __syncthreads();
+  if (valid) {
+    const int l0 = j + 16 * (i >> 2), l1 = H == 16 ? l0 + 8 : j + 8 + 16 * ((i + 8) >> 2), v = i & 3;
+    float s[kWaves];
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) s[w] = part[w][0][v][l0] + part[w][H == 16 ? 1 : 0][v][l1];
+    store_y<T>(p.y, j * p.ldy + row0 + i, p.y_f32,
+               apply_epi(((s[0] + s[1]) + (s[2] + s[3])) + T::to_f32(bias_v), p.epi, T::to_f32(resid_v)));
   }
 }
 
@@ -1814,6 +1974,51 @@ hipError_t launch_gemv_mfma(GemvParams p, int dtype, int B, hipStream_t stream) 
     return hipErrorInvalidValue;
   if (p.ln) return dtype == 1 ? launch_mfma_t<BF16, true>(p, B, G, stream) : launch_mfma_t<F16, true>(p, B, G, stream);
   return dtype == 1 ? launch_mfma_t<BF16, false>(p, B, G, stream) : launch_mfma_t<F16, false>(p, B, G, stream);
+}
+
+template <class T, int H>
+hipError_t launch_rows_k(const GemvParams& p, int B, hipStream_t s) {
+  hipLaunchKernelGGL((gemv_rows_kernel<T, H>), dim3((p.rows + H - 1) / H), dim3(kThreads), 0, s, p, B);
+  return hipGetLastError();
+}
+
+// Resident row-major rows on the matrix cores: from B = 2 on, where the vector GEMV is bound
+// by its products and its reads of x (us, vector / matrix cores, B = 2, 4 and 8: [16384, 4096]
+// 26.2 / 23.6, 24.8 / 23.9, 31.5 / 24.9; [10007, 5128] 27.5 / 19.7, 22.3 / 20.1, 35.2 / 23.7;
+// [4096, 4096] 9.1 / 8.1, 9.9 / 8.4, 12.7 / 8.6; [2560, 10240] 13.8 / 13.2, 14.9 / 12.9, 21.2 /
+// 14.4; [32000, 264] 17.3 / 9.8, 13.6 / 9.8, 18.7 / 10.4), and at B = 1 for many rows, which
+// there are several to a wavefront ([36864, 9216] 111.1 / 97.9, [20480, 5120] 35.8 / 33.3, but
+// [16384, 4096] 22.1 / 23.8).  Few rows leave CUs idle sooner than with one row per wavefront:
+// up to 1024 rows from B = 3 ([1000, 4096] 4.2 / 4.4 at B = 2, 5.3 / 4.7 at 4, 9.0 / 5.3 at
+// 8), up to 512 long rows from B = 5 ([100, 16384] 9.2 / 9.6 at B = 4, 17.5 / 9.8 at 5).  An x too
+// large for its buffer descriptor stays on the vector GEMV.
+bool gemv_rows_wanted(int rows, int K, long long ldx, int B) {
+  if (B < 1 || B > kLnSlots || ((long long)(B - 1) * ldx + K) * 2 >= (long long)kXPast) return false;
+  if (rows <= kRowsFew / 2 && K > kRowsLongK) return B >= 5;
+  if (rows <= kRowsFew) return B >= 3;
+  return B >= 2 || rows > kRowsMany;
+}
+
+// Rows per workgroup: 8 (twice the workgroups, x read as often as W) when 16 would leave more
+// than half of the CUs idle, load them unevenly, or leave one or two workgroups per CU on long
+// rows; 16 otherwise and on rows too short for four wavefronts of 512 columns (us, 8 / 16
+// rows, B = 4: [1000, 4096] 4.7 / 5.6, [10007, 5128] 20.0 / 21.2, [6000, 6000] 14.6 / 16.1,
+// [4096, 16384] 27.6 / 29.3; [20480, 5120] 35.5 / 31.7, [8192, 2048] 9.1 / 8.4, [32000, 264]
+// 15.7 / 9.8).
+static bool rows_by_8(int rows, int K) {
+  const int n16 = (rows + 15) / 16, cus = device_cus();
+  if (K < kRowsMinK8) return false;
+  return n16 <= cus / 2 || (n16 > cus && uneven(n16, cus) > kRowsUneven) ||
+         (K >= kRowsLongK && n16 % cus == 0 && n16 <= 2 * cus);
+}
+
+hipError_t launch_gemv_rows(GemvParams p, int dtype, int B, hipStream_t stream) {
+  if (p.rows <= 0) return hipSuccess;
+  if (p.K < 8 || p.K % 8 || B < 1 || B > kLnSlots || p.ln || p.segmajor) return hipErrorInvalidValue;
+  if (p.ldx < p.K || ((long long)(B - 1) * p.ldx + p.K) * 2 >= (long long)kXPast) return hipErrorInvalidValue;
+  if (rows_by_8(p.rows, p.K))
+    return dtype == 1 ? launch_rows_k<BF16, 8>(p, B, stream) : launch_rows_k<F16, 8>(p, B, stream);
+  return dtype == 1 ? launch_rows_k<BF16, 16>(p, B, stream) : launch_rows_k<F16, 16>(p, B, stream);
 }
 
 }  // namespace hg
