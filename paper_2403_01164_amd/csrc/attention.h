@@ -25,7 +25,7 @@ struct AttnParams {
   uint32_t* cnt;
   int heads, head_dim, max_seq, max_chunks, pos;
   int nchunk;   // set by the launcher
-  float scale;  // set by the launcher: 1 / sqrt(head_dim)
+  float scale;  // set by the launcher: log2(e) / sqrt(head_dim)
 };
 
 // Positions per workgroup of the attention kernel for short caches (the smallest chunk:

@@ -9,17 +9,25 @@
 // is bound by HBM bandwidth (2 * (pos + 1) * D * 2 bytes per (b, h)), not by
 // arithmetic; no matrix cores.
 //
-// Split over positions: workgroup (c, h, b) takes the 64 positions of chunk c (128
-// from 2048 cached positions on: fewer partials to merge, 13-35 % faster at 2048 and
-// 4096 positions, slower below at batch 8; the size depends on the position alone, so a
-// batch row's bits do not depend on the batch size), 4 wavefronts x 64 / (D / 8) positions
-// per round (D / 8 lanes hold one 16-byte
-// slice each of a key or value row, so a load instruction reads whole 256-byte
-// rows, coalesced).  It keeps (max score, sum of exponentials, weighted sum of V)
-// of its chunk; the last workgroup of (b, h) to finish (an arrival counter, no
+// Split over positions: workgroup (c, h, b) takes the positions of chunk c, D / 8 lanes per
+// key or value row (a 16-byte slice each, so a load instruction reads whole rows, coalesced),
+// and requests all of its rows at once.  Each wavefront scores its own rows (row sums by DPP,
+// the largest by readlane), exponentiates against its own maximum and sums its value rows;
+// the wavefronts meet once, in LDS.  The workgroup's (max score, sum of exponentials, weighted
+// sum of V) goes to memory and the last workgroup of (b, h) to finish (an arrival counter, no
 // waiting) merges the chunks in chunk order and writes the output rounded to the
-// activation type.  Every reduction has a fixed order, so results are
-// deterministic.
+// activation type.  Every reduction has a fixed order, so results are deterministic.
+//
+// What bounds it: a chain of memory round trips at one sequence (rows, partial and arrival,
+// merge), the bandwidth at eight long ones.  Chunks: 64 positions for short caches, 128 from
+// 384 positions on (fewer partials to merge), 256 from 2048; the size depends on the position
+// alone, so a batch row's bits do not depend on the batch size.  32 heads of 128, us, 64 / 128
+// / 256 positions per chunk: 1 sequence, 201 positions 5.3 / 5.7 / -, 513 7.6 / 6.7 / 7.7, 1001
+// 10.0 / 8.0 / 8.5, 4096 - / 21.9 / 16.5; 8 sequences, 513 positions 16.1 / 15.9 / 18.0, 1001
+// 28.9 / 26.3 / 26.5, 4096 - / 104 / 95.7 (5.6 TB/s); 8 x 40 heads, 2049 positions - / 63.5 / 59.3.
+// With the scores exchanged through LDS, one wavefront's softmax for the workgroup and sums by
+// ds_bpermute the same cases took, at 64 (128 from 2048) positions per chunk, 6.4, 9.0, 11.6, 24.2;
+// 18.0, 31.6, 111; 69.8.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -29,20 +37,63 @@
 namespace hg {
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kWaves = kThreads / 64;
-constexpr int kChunk = 64;       // positions per workgroup, short caches
-constexpr int kLongChunk = 128;  // positions per workgroup from kLongFrom positions on
+constexpr int kThreads = 256;    // kv_copy_kernel
+constexpr int kChunk = 64;       // positions per workgroup (256 threads), short caches
+constexpr int kMidChunk = 128;   // positions per workgroup (512 threads) from kMidFrom positions on
+constexpr int kMidFrom = 384;
+constexpr int kLongChunk = 256;  // positions per workgroup (512 threads) from kLongFrom positions on
 constexpr int kLongFrom = 2048;
-constexpr int kMaxChunks = 256;  // chunks the merge holds in LDS (positions <= 16384)
+constexpr int kMaxChunks = 256;  // chunks the merge holds in LDS; kChunk * kMaxChunks: the longest cache
 constexpr int kMergeRegs = 16;   // chunks whose partial outputs the merge requests at once
 
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+
+// Query: dot(k) is a lane's 8 products of q with a key row's 16 bytes, finish() the row's
+// score (in the log2 domain) from their sum.  fp16 multiplies pairs (exact products, binary32
+// sums) and scales the sum; bf16 scales q first, in binary32: products of its largest values
+// would overflow before they are scaled.
 struct F16 {
+  struct Query {
+    uint4 q;
+    float scale;
+    __device__ __forceinline__ Query(const uint4& v, float s) : q(v), scale(s) {}
+    __device__ __forceinline__ float dot(const uint4& k) const {
+      float d = 0.f;
+      const uint32_t a[4] = {q.x, q.y, q.z, q.w}, b[4] = {k.x, k.y, k.z, k.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        d = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, a[i]), __builtin_bit_cast(f16x2, b[i]), d, false);
+      return d;
+    }
+    __device__ __forceinline__ float finish(float sum) const { return sum * scale; }
+  };
   static __device__ __forceinline__ float to_f32(uint16_t h) { return (float)__builtin_bit_cast(_Float16, h); }
   static __device__ __forceinline__ uint16_t from_f32(float v) { return __builtin_bit_cast(uint16_t, (_Float16)v); }
 };
 
 struct BF16 {
+  struct Query {
+    float q[8];
+    __device__ __forceinline__ Query(const uint4& v, float s) {
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        q[2 * i] = __builtin_bit_cast(float, w[i] << 16) * s;
+        q[2 * i + 1] = __builtin_bit_cast(float, w[i] & 0xFFFF0000u) * s;
+      }
+    }
+    __device__ __forceinline__ float dot(const uint4& k) const {
+      float d = 0.f;
+      const uint32_t w[4] = {k.x, k.y, k.z, k.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        d = fmaf(q[2 * i], __builtin_bit_cast(float, w[i] << 16), d);
+        d = fmaf(q[2 * i + 1], __builtin_bit_cast(float, w[i] & 0xFFFF0000u), d);
+      }
+      return d;
+    }
+    __device__ __forceinline__ float finish(float sum) const { return sum; }
+  };
   static __device__ __forceinline__ float to_f32(uint16_t h) { return __builtin_bit_cast(float, (uint32_t)h << 16); }
   static __device__ __forceinline__ uint16_t from_f32(float v) { return __builtin_bit_cast(uint16_t, (__bf16)v); }
 };
@@ -78,33 +129,45 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, uint32_t b
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
 }
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
+// v + v of the lane the DPP control names (0xB1 lane ^ 1, 0x4E lane ^ 2, 0x141 mirrored half
+// row, 0x140 mirrored row of 16).
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
+}
+
+// Sum over the LP (8 or 16) lanes that hold one row, in every lane of the row.
+template <int LP>
+__device__ __forceinline__ float row_sum(float v) {
+  v += dpp<0xB1>(v);
+  v += dpp<0x4E>(v);
+  v += dpp<0x141>(v);
+  if (LP == 16) v += dpp<0x140>(v);
   return v;
 }
 
-__device__ __forceinline__ float wave_add(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-  return v;
+__device__ __forceinline__ float lane_value(float v, int lane) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
 }
 
-template <class T, int D, int CH>
-__global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams a) {
+__device__ __forceinline__ float exp2_hw(float v) { return __builtin_amdgcn_exp2f(v); }
+
+// A workgroup's chunk: scores in the log2 domain (scale includes log2 e), m = their largest,
+// p = 2^(s - m), l = sum of p, o = sum of p V.
+template <class T, int D, int CH, int NT>
+__global__ __launch_bounds__(NT) void attn_kernel(AttnParams a) {
+  constexpr int kWaves = NT / 64;
   constexpr int LP = D / 8;          // lanes per key/value row
   constexpr int PPW = 64 / LP;       // rows per wavefront per round
   constexpr int PPR = PPW * kWaves;  // rows per workgroup per round
   constexpr int ROUNDS = CH / PPR;
-  constexpr int SPL = CH / 64;       // scores per lane of the softmax wavefront
-  __shared__ float sp[CH];
-  __shared__ float sacc[kWaves][D];
-  __shared__ float sml[2];
+  __shared__ __align__(16) float sacc[kWaves * PPW][D + 4];
+  __shared__ float sl[kWaves * PPW], sm[kWaves];
   __shared__ float s_m[kMaxChunks], s_l[kMaxChunks];
   __shared__ int s_last;
 
   const int c = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int sub = lane % LP, grp = lane / LP;
   const int H = a.heads * D;
   const uint16_t* qkv = (const uint16_t*)a.qkv + (size_t)b * a.ldq;
@@ -115,91 +178,84 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams a) {
   uint16_t* Vc = (uint16_t*)a.vc + head * D;
   const int j0 = c * CH;
 
-  // every key and value row of the chunk is requested at once (positions past pos
-  // reread the new token's row and are masked below); position pos comes from qkv
+  // q, then every key and value row of the chunk is requested at once, the keys first
+  // (positions past pos reread the new token's row and are masked below; position pos
+  // comes from qkv)
+  const uint4 qv = load16<false>(qkv + h * D + sub * 8);
   uint4 kr[ROUNDS], vr[ROUNDS];
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
     const int j = j0 + r * PPR + wave * PPW + grp;
-    kr[r] = j >= a.pos ? load16<false>(knew + sub * 8) : load16<true>(Kc + (size_t)j * D + sub * 8);
-    vr[r] = j >= a.pos ? load16<false>(vnew + sub * 8) : load16<true>(Vc + (size_t)j * D + sub * 8);
+    kr[r] = load16<true>((j >= a.pos ? knew : Kc + (size_t)j * D) + sub * 8);
   }
-  float q[8];
-  unpack8<T>(load16<false>(qkv + h * D + sub * 8), q);
-#pragma unroll
-  for (int e = 0; e < 8; ++e) q[e] *= a.scale;
-
-  // the chunk holding pos appends the new key and value to the cache
-  if (c == a.nchunk - 1 && threadIdx.x < 2 * LP) {
-    const int s = threadIdx.x % LP;
-    if (threadIdx.x < LP) *(uint4*)(Kc + (size_t)a.pos * D + s * 8) = load16<false>(knew + s * 8);
-    else *(uint4*)(Vc + (size_t)a.pos * D + s * 8) = load16<false>(vnew + s * 8);
-  }
-
-  // scores of the chunk's positions
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
-    const int jl = r * PPR + wave * PPW + grp;
-    float k[8];
-    unpack8<T>(kr[r], k);
-    float s = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) s = fmaf(q[e], k[e], s);
-#pragma unroll
-    for (int off = LP / 2; off >= 1; off >>= 1) s += __shfl_xor(s, off);  // the LP lanes of one row
-    if (sub == 0) sp[jl] = j0 + jl <= a.pos ? s : -INFINITY;
+    const int j = j0 + r * PPR + wave * PPW + grp;
+    vr[r] = load16<true>((j >= a.pos ? vnew : Vc + (size_t)j * D) + sub * 8);
   }
-  __syncthreads();
-  if (wave == 0) {  // scores lane + 64 i of the chunk
-    float sv[SPL], mx = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < SPL; ++i) {
-      sv[i] = sp[lane + 64 * i];
-      mx = fmaxf(mx, sv[i]);
-    }
-    const float m = wave_max(mx);
-    float ps = 0.f;
-#pragma unroll
-    for (int i = 0; i < SPL; ++i) {
-      const float p = sv[i] == -INFINITY ? 0.f : expf(sv[i] - m);
-      sp[lane + 64 * i] = p;
-      ps += p;
-    }
-    const float l = wave_add(ps);
-    if (lane == 0) {
-      sml[0] = m;
-      sml[1] = l;
-    }
-  }
-  __syncthreads();
 
-  // weighted sum of the chunk's value rows (masked positions have weight 0)
-  float acc[8];
+  // scores of this wavefront's positions, every lane of a row holding its row's
+  const typename T::Query q(qv, a.scale);
+  float s[ROUNDS], m = -INFINITY;
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    const int j = j0 + r * PPR + wave * PPW + grp;
+    s[r] = j <= a.pos ? q.finish(row_sum<LP>(q.dot(kr[r]))) : -INFINITY;
+    m = fmaxf(m, s[r]);
+  }
+  if (LP == 8) m = fmaxf(m, dpp<0x140>(m));  // the two rows of a 16-lane row
+  m = fmaxf(fmaxf(lane_value(m, 0), lane_value(m, 16)), fmaxf(lane_value(m, 32), lane_value(m, 48)));
+
+  // weighted sum of its value rows (masked positions have weight 0)
+  float l = 0.f, acc[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] = 0.f;
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
-    const float p = sp[r * PPR + wave * PPW + grp];
+    const float p = s[r] == -INFINITY ? 0.f : exp2_hw(s[r] - m);
+    l += p;
     float v[8];
     unpack8<T>(vr[r], v);
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = fmaf(p, v[e], acc[e]);
   }
-#pragma unroll
-  for (int off = LP; off < 64; off <<= 1)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] += __shfl_xor(acc[e], off);
-  if (grp == 0)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) sacc[wave][sub * 8 + e] = acc[e];
+  const int slot = wave * PPW + grp;
+  *(float4*)&sacc[slot][sub * 8] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+  *(float4*)&sacc[slot][sub * 8 + 4] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+  if (sub == 0) sl[slot] = l;
+  if (lane == 0) sm[wave] = m;
+
+  // the chunk holding pos appends the new key and value to the cache
+  if (c == a.nchunk - 1 && threadIdx.x < 2 * LP) {
+    const int e = threadIdx.x % LP * 8;
+    if (threadIdx.x < LP) *(uint4*)(Kc + (size_t)a.pos * D + e) = load16<false>(knew + e);
+    else *(uint4*)(Vc + (size_t)a.pos * D + e) = load16<false>(vnew + e);
+  }
   __syncthreads();
 
+  // the wavefronts' sums, in order (one without a valid position has m = -inf, weight 0)
   const int t = threadIdx.x;
-  float o = 0.f;
-  if (t < D) o = (sacc[0][t] + sacc[1][t]) + (sacc[2][t] + sacc[3][t]);
+  float M = sm[0];
+#pragma unroll
+  for (int w = 1; w < kWaves; ++w) M = fmaxf(M, sm[w]);
+  float o = 0.f, L = 0.f;
+  if (t < D) {
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const float f = sm[w] == -INFINITY ? 0.f : exp2_hw(sm[w] - M);
+      float so = 0.f, ss = 0.f;
+#pragma unroll
+      for (int g = 0; g < PPW; ++g) {
+        so += sacc[w * PPW + g][t];
+        ss += sl[w * PPW + g];
+      }
+      o = fmaf(f, so, o);
+      L = fmaf(f, ss, L);
+    }
+  }
   uint16_t* out = (uint16_t*)a.out + (size_t)b * a.ldo + h * D;
   if (a.nchunk == 1) {
-    if (t < D) out[t] = T::from_f32(o / sml[1]);
+    if (t < D) out[t] = T::from_f32(o / L);
     return;
   }
 
@@ -211,8 +267,8 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams a) {
   if (t < D) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, o), rs, (mine + 2 + t) * 4, 0,
                                                    kCoherent);
   if (t == 0) {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, sml[0]), rs, mine * 4, 0, kCoherent);
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, sml[1]), rs, (mine + 1) * 4, 0, kCoherent);
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, M), rs, mine * 4, 0, kCoherent);
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, L), rs, (mine + 1) * 4, 0, kCoherent);
   }
   __builtin_amdgcn_s_waitcnt(0);  // this thread's partial stores have completed
   __syncthreads();
@@ -234,15 +290,15 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams a) {
 #pragma unroll
     for (int u = 0; u < kMergeRegs; ++u) ov[u] = u < a.nchunk ? ld(u * (D + 2) + 2 + t) : 0.f;
   }
-  for (int k = t; k < a.nchunk; k += kThreads) {
+  for (int k = t; k < a.nchunk; k += NT) {
     s_m[k] = ld(k * (D + 2));
     s_l[k] = ld(k * (D + 2) + 1);
   }
   __syncthreads();
   if (t < D) {
-    float M = -INFINITY;
-    for (int k = 0; k < a.nchunk; ++k) M = fmaxf(M, s_m[k]);
-    float L = 0.f, O = 0.f;
+    float Mx = -INFINITY;
+    for (int k = 0; k < a.nchunk; ++k) Mx = fmaxf(Mx, s_m[k]);
+    float Ls = 0.f, O = 0.f;
     for (int k0 = 0; k0 < a.nchunk; k0 += kMergeRegs) {
       if (k0 > 0) {
 #pragma unroll
@@ -251,22 +307,31 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams a) {
 #pragma unroll
       for (int u = 0; u < kMergeRegs; ++u) {
         if (k0 + u < a.nchunk) {
-          const float w = expf(s_m[k0 + u] - M);
-          L = fmaf(s_l[k0 + u], w, L);
+          const float w = exp2_hw(s_m[k0 + u] - Mx);
+          Ls = fmaf(s_l[k0 + u], w, Ls);
           O = fmaf(ov[u], w, O);
         }
       }
     }
-    out[t] = T::from_f32(O / L);
+    out[t] = T::from_f32(O / Ls);
   }
 }
 
-template <class T, int CH>
+template <class T, int CH, int NT>
 hipError_t launch_t(const AttnParams& a, int B, hipStream_t s) {
   const dim3 grid(a.nchunk, a.heads, B);
-  if (a.head_dim == 128) hipLaunchKernelGGL((attn_kernel<T, 128, CH>), grid, dim3(kThreads), 0, s, a);
-  else hipLaunchKernelGGL((attn_kernel<T, 64, CH>), grid, dim3(kThreads), 0, s, a);
+  if (a.head_dim == 128) hipLaunchKernelGGL((attn_kernel<T, 128, CH, NT>), grid, dim3(NT), 0, s, a);
+  else hipLaunchKernelGGL((attn_kernel<T, 64, CH, NT>), grid, dim3(NT), 0, s, a);
   return hipGetLastError();
+}
+
+template <class T>
+hipError_t launch_ch(const AttnParams& a, int ch, int B, hipStream_t s) {
+  switch (ch) {
+    case kChunk: return launch_t<T, kChunk, 256>(a, B, s);
+    case kMidChunk: return launch_t<T, kMidChunk, 512>(a, B, s);
+  }
+  return launch_t<T, kLongChunk, 512>(a, B, s);
 }
 
 // Positions [pos0, pos0 + n) of one layer between the cache and token-major buffers of the
@@ -325,13 +390,11 @@ int attn_max_positions() { return kChunk * kMaxChunks; }
 hipError_t launch_attention(AttnParams a, int dtype, int B, hipStream_t stream) {
   if (B < 1 || a.pos < 0 || a.pos >= a.max_seq || (a.head_dim != 64 && a.head_dim != 128) || a.heads < 1)
     return hipErrorInvalidValue;
-  const bool lng = a.pos + 1 >= kLongFrom;
-  const int ch = lng ? kLongChunk : kChunk;
+  const int ch = a.pos + 1 >= kLongFrom ? kLongChunk : a.pos + 1 >= kMidFrom ? kMidChunk : kChunk;
   a.nchunk = (a.pos + ch) / ch;  // chunks covering positions [0, pos]
   if (a.nchunk > a.max_chunks || a.nchunk > kMaxChunks) return hipErrorInvalidValue;
-  a.scale = 1.0f / sqrtf((float)a.head_dim);
-  if (lng) return dtype == 1 ? launch_t<BF16, kLongChunk>(a, B, stream) : launch_t<F16, kLongChunk>(a, B, stream);
-  return dtype == 1 ? launch_t<BF16, kChunk>(a, B, stream) : launch_t<F16, kChunk>(a, B, stream);
+  a.scale = 1.4426950408889634f / sqrtf((float)a.head_dim);  // log2 e / sqrt(D)
+  return dtype == 1 ? launch_ch<BF16>(a, ch, B, stream) : launch_ch<F16>(a, ch, B, stream);
 }
 
 hipError_t launch_kv_copy(const KvCopyParams& a, int B, bool to_cache, hipStream_t stream) {
