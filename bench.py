@@ -369,14 +369,14 @@ def table2_linear(args, torch, synth, hg):
 
 def mfma_splits(rows, K, cus):
     """Splits of the sum over K in the matrix-core GEMV on a device of `cus` compute units
-    (the library's rule: unsplit unless one workgroup per 16-row tile loads the units more
-    than 1.15x unevenly; then the fewest splits of at least 32 k-tiles that do not, or the
-    most even)."""
+    (the library's rule: unsplit below 128 k-tiles, or unless one workgroup per 16-row tile
+    loads the units more than 1.15x unevenly, 1.3x below 256 k-tiles; then the fewest splits of
+    at least 32 k-tiles that load them within 1.15x, or the most even)."""
     def uneven(wgs):
         return -(-wgs // cus) * cus / wgs
     rt, kt = -(-rows // 16), -(-K // 32)
     best, best_u = 1, uneven(rt)
-    if best_u <= 1.15:
+    if best_u <= 1.15 or kt < 128 or (kt < 256 and best_u <= 1.3):
         return 1
     g = 2
     while g <= 8 and kt // g >= 32:
@@ -403,6 +403,8 @@ def mfma_rows(rows, K, g, ln, cus):
     load = lambda r: -(-(-(-rt // r) * g) // cus) * r
     even = rt * g % cus == 0
     if g > 1:
+        if even and not ln and kt // g < 128 and 5 * load(3) <= 6 * load(1):
+            return 3
         return 5 if load(5) <= load(1) and (ln or not even or kt // g >= 128) else 1
     if even and not ln:
         return 2 if rt % (2 * cus) == 0 and rt <= 4 * cus else 1

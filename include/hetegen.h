@@ -159,8 +159,9 @@ HETEGEN_API hetegen_status hetegen_tile_weights(hetegen_ctx* ctx, const void* W_
  * and N) as in hetegen_linear; bias_dev optional device [N].  Binary32 sums (the
  * matrix core's products of 16-bit values are exact).  When one workgroup per 16-row
  * tile would load the device's compute units unevenly (the busiest more than 1.15x
- * the mean), the sum over K is split over up to 8 workgroups (each at least 32
- * 32-column tiles long) whose partial sums are added in a fixed order: the split
+ * the mean, 1.3x for K <= 8160) and K > 4064, the sum over K is split over up to 8
+ * workgroups (each at least 32 32-column tiles long) whose partial sums are added in a
+ * fixed order: the split
  * depends on N, K and the device's compute-unit count, not on B or timing, so a
  * batch row's bits do not depend on the batch size.  Uses the context's split-K
  * workspace, which the first call with a larger need allocates (device memory,
@@ -179,7 +180,8 @@ HETEGEN_API hetegen_status hetegen_linear_tiled(hetegen_ctx* ctx, const void* x_
  * hetegen_create and held until the process ends (262144 floats of partials and
  * 65536 counters, 1.25 MiB per GPU).  The call allocates nothing; it returns
  * UNSUPPORTED, without launching, for a shape whose split (see hetegen_linear_tiled)
- * needs more than that, i.e. ceil(N / 16) * splits * 16 * B floats.  On a 256-CU
+ * would need more than that, i.e. ceil(N / 16) * splits * 16 * B floats with the splits that
+ * an even load (1.15x) would take at any K.  On a 256-CU
  * device every linear of OPT-6.7B to OPT-175B fits at batch 8 (the largest need,
  * OPT-13B's [5120, 5120] and [5120, 20480] in 4 splits, is 163840 floats); a split
  * linear of more than 1024 row tiles at batch 8, such as [16400, 36864], does not.  Every

@@ -755,9 +755,11 @@ __device__ __forceinline__ uint4 normalize8_fma(const uint4& v, float a, float c
 
 constexpr int kTileRows = 16, kTileK = 32;
 constexpr int kChunkTiles = 4;  // k-tiles dealt to a wavefront at a time
-// K-split choice of the matrix-core GEMV (mfma_splits)
+// K-split choice of the matrix-core GEMV (even_splits, splits_on)
 constexpr double kMaxUneven = 1.15;  // busiest CU's workgroups over the mean, tolerated unsplit
 constexpr int kMaxSplits = 8, kMinSplitTiles = 32;
+constexpr int kMinTilesToSplit = 128, kLongTiles = 256;  // k-tiles of a row
+constexpr double kMaxUnevenShort = 1.3;                   // below kLongTiles
 constexpr int kMaxDevices = 64, kDefaultCus = 256;
 constexpr int kMaxKmajorPerCu = 3;  // mfma_kmajor
 constexpr int kLongSplitTiles = 128;  // mfma_rows
@@ -1860,19 +1862,13 @@ static double uneven(long long wgs, int cus) {
   return (double)(per * cus) / (double)wgs;
 }
 
-// One row tile per workgroup unless that loads the CUs unevenly (more than 1.15x the
-// mean on the busiest); then the fewest splits that do not, each at least 32 k-tiles
-// long, or else the most even split.  Splitting a balanced grid only adds the merge:
-// OPT-6.7B fc2 [4096, 16384] (256 row tiles) at B = 8 takes 23.9 us unsplit against
-// 26.2 us in 4 splits; OPT-13B fc2 [5120, 20480] (320 row tiles) 49.4 unsplit against
-// 39.1 us in 4 splits.  Over the 16 linear shapes of OPT-6.7B/13B/30B/66B at B = 1, 2, 3
-// and 8 the rule picks the fastest split count but at B = 8 for OPT-13B out [5120, 5120]
-// (4 splits: 15.5 against 14.8 us with 2) and OPT-66B fc2 [9216, 36864] (2 splits: 117.3
-// against 114.0 us with 4).  The choice does not depend on B, so a batch row's bits do not
-// either.
-int mfma_splits(int rows, int K) {
+// The most K-splits a linear takes, by evenness alone: one workgroup per row tile unless that
+// loads the CUs unevenly (more than 1.15x the mean on the busiest); then the fewest splits
+// that do not, each at least 32 k-tiles long, or else the most even split.  Workspaces are
+// sized by it.
+static int even_splits(int rows, int K, int cus) {
   if (rows <= 0 || K <= 0) return 1;
-  const int KT = (K + kTileK - 1) / kTileK, RT = (rows + kTileRows - 1) / kTileRows, cus = device_cus();
+  const int KT = (K + kTileK - 1) / kTileK, RT = (rows + kTileRows - 1) / kTileRows;
   double best_u = uneven(RT, cus);
   if (best_u <= kMaxUneven) return 1;
   int best = 1;
@@ -1887,6 +1883,23 @@ int mfma_splits(int rows, int K) {
   return best;
 }
 
+// K-splits of a launch.  Splitting pays for an uneven grid only when K is long enough: the merge
+// (partial store, arrival, loads) costs about 1.5 us at the tail.  Rows of fewer than 4096
+// columns are not split ([2048, 2048] 4.8 us unsplit against 5.7 in 2, [768, 3072] 4.8 / 5.6,
+// [10240, 2560] with the LayerNorm 11.4 / 13.6, all at B = 2 or 4), rows of fewer than 8192
+// only above 1.3x ([13000, 4360] with the LayerNorm 21.5 us unsplit against 24.8 in 2,
+// [10007, 5128] 18.9 / 20.4; [5120, 5120], 1.6x, takes 4).  Long rows by evenness: OPT-13B fc2
+// [5120, 20480] (320 row tiles) took 49.4 us unsplit and 39.1 in 4 splits, OPT-6.7B fc2 [4096,
+// 16384] (256 row tiles, even) 23.9 unsplit and 26.2 in 4.  The choice does not depend on B, so
+// a batch row's bits do not either.
+static int splits_on(int rows, int K, int cus) {
+  const int KT = (K + kTileK - 1) / kTileK, RT = (rows + kTileRows - 1) / kTileRows;
+  if (KT < kMinTilesToSplit || (KT < kLongTiles && uneven(RT, cus) <= kMaxUnevenShort)) return 1;
+  return even_splits(rows, K, cus);
+}
+
+int mfma_splits(int rows, int K) { return rows <= 0 || K <= 0 ? 1 : splits_on(rows, K, device_cus()); }
+
 // k-major tiles when the row tiles and splits put the same number of workgroups, 1 to 3, on
 // every CU: all of them then start together and walk K side by side, and in row-tile order
 // their loads would fall on the same offsets of blocks a fixed multiple of 16 rows apart,
@@ -1897,19 +1910,19 @@ int mfma_splits(int rows, int K) {
 // 23.5 us; OPT-30B fc1 [28672, 7168], 7 per CU: 70.5 / 72.8).
 int mfma_kmajor(int rows, int K) {
   if (rows <= 0 || K <= 0) return 0;
-  const long long wgs = (long long)((rows + kTileRows - 1) / kTileRows) * mfma_splits(rows, K);
   const int cus = device_cus();
+  const long long wgs = (long long)((rows + kTileRows - 1) / kTileRows) * splits_on(rows, K, cus);
   return wgs % cus == 0 && wgs / cus <= kMaxKmajorPerCu ? 1 : 0;
 }
 
 size_t mfma_ws_floats(int rows, int K, int B) {
-  const int G = mfma_splits(rows, K);
+  const int G = even_splits(rows, K, device_cus());
   if (G == 1 || rows <= 0) return 0;
   return (size_t)((rows + kTileRows - 1) / kTileRows) * G * kTileRows * B;
 }
 
 size_t mfma_cnt_words(int rows, int K) {
-  if (mfma_splits(rows, K) == 1 || rows <= 0) return 0;
+  if (rows <= 0 || even_splits(rows, K, device_cus()) == 1) return 0;
   return (size_t)((rows + kTileRows - 1) / kTileRows);
 }
 
@@ -1918,19 +1931,24 @@ size_t mfma_cnt_words(int rows, int K) {
 // ceil(workgroups / CUs) * R row tiles, and R is taken only where that is no more than with
 // one row tile per workgroup.  Unsplit: the largest such R up to 3; where one row tile per
 // workgroup already loads the CUs evenly and there is no LayerNorm, only 2 for grids of 2
-// or 4 per CU ([8192, 4096] 15.1 -> 12.5 us, [16384, 4096] 23.2 -> 22.9; none of 3, 6 or 8).  Split: 5 or 1 (5
-// brings the OPT-66B grids, 1152 workgroups, to 232, all running at once), 5 only with the
-// LayerNorm, on an uneven grid or for long splits: the merge of 5 row tiles costs more than
-// of one.  Measured at B = 8 (us, R = 1 / 2 / 3 / 5): [15360, 5120] with the LayerNorm 29.0
-// / 27.0 / 33.6 / 30.1, [16384, 4096] with it 25.2 / 23.5 / 27.8 / 25.0, [7168, 28672] 70.2
-// / 65.2 / 79.4 / 115, [21504, 7168] 51.7 / 51.0 / 50.2 / 70.5, [28672, 7168] 64.1 / 67.8 /
-// 72.3 / 79.7; split [9216, 36864] in 2 115 / 120 / 120 / 105, [5120, 20480] in 4 39.6 /
-// 39.8 / 38.8 / 38.2, [5120, 5120] in 4 14.1 / 15.7 / 13.9 / 14.5.  R does not change the bits.
-int mfma_rows(int rows, int K, int G, bool ln) {
-  const int KT = (K + kTileK - 1) / kTileK, RT = (rows + kTileRows - 1) / kTileRows, cus = device_cus();
+// or 4 per CU ([8192, 4096] 15.1 -> 12.5 us, [16384, 4096] 23.2 -> 22.9; none of 3, 6 or 8).
+// Split: 5 on an uneven grid, with the LayerNorm or for long splits (it brings the OPT-66B
+// grids, 1152 workgroups, to 232, all running at once), 3 for short splits of an even grid up
+// to a fifth more per CU (the workgroups of an even grid in row-tile order walk K in step and
+// crowd a few memory channels), else 1.  Measured at B = 8 (us, R = 1 / 2 / 3 / 5): [15360,
+// 5120] with the LayerNorm 29.0 / 27.0 / 33.6 / 30.1, [16384, 4096] with it 25.2 / 23.5 / 27.8
+// / 25.0, [7168, 28672] 70.2 / 65.2 / 79.4 / 115, [21504, 7168] 51.7 / 51.0 / 50.2 / 70.5,
+// [28672, 7168] 64.1 / 67.8 / 72.3 / 79.7; split [9216, 36864] in 2 115 / 120 / 120 / 105,
+// [5120, 20480] in 4 39.6 / 39.8 / 38.8 / 38.2, [5120, 5120] in 4 14.0 / 15.6 / 13.2 / 14.5,
+// [2560, 10240] in 8 14.5 / 15.5 / 13.5 / 14.6.  R does not change the bits.
+static int mfma_rows(int rows, int K, int G, bool ln, int cus) {
+  const int KT = (K + kTileK - 1) / kTileK, RT = (rows + kTileRows - 1) / kTileRows;
   auto load = [&](int r) { return ((long long)(RT + r - 1) / r * G + cus - 1) / cus * r; };
   const bool even = (long long)RT * G % cus == 0;
-  if (G > 1) return load(5) <= load(1) && (ln || !even || KT / G >= kLongSplitTiles) ? 5 : 1;
+  if (G > 1) {
+    if (even && !ln && KT / G < kLongSplitTiles && 5 * load(3) <= 6 * load(1)) return 3;
+    return load(5) <= load(1) && (ln || !even || KT / G >= kLongSplitTiles) ? 5 : 1;
+  }
   if (even && !ln) return RT % (2 * cus) == 0 && RT <= 4 * cus ? 2 : 1;
   if (load(3) <= std::min(load(1), load(2))) return 3;
   return load(2) <= load(1) ? 2 : 1;
@@ -1949,14 +1967,14 @@ hipError_t launch_mfma_k(const GemvParams& p, int B, int G, hipStream_t s) {
 // ([4096, 1024] 4.55 against 5.05 us with 4: its whole K is one request) or rows long enough
 // to pay for it ([20480, 5120] 36.2 against 37.0, but [12288, 4096] 18.7 against 18.4).
 template <class T, bool LN>
-hipError_t launch_mfma_t(const GemvParams& p, int B, int G, hipStream_t s) {
+hipError_t launch_mfma_t(const GemvParams& p, int B, int G, int cus, hipStream_t s) {
   const int RT = (p.rows + kTileRows - 1) / kTileRows;
-  switch (mfma_rows(p.rows, p.K, G, LN)) {
+  switch (mfma_rows(p.rows, p.K, G, LN, cus)) {
     case 5: return launch_mfma_k<T, 4, 5, LN>(p, B, G, s);
     case 3: return launch_mfma_k<T, 4, 3, LN>(p, B, G, s);
     case 2: return launch_mfma_k<T, 4, 2, LN>(p, B, G, s);
   }
-  const bool u8 = G == 1 && (!LN || RT <= device_cus() || p.K > kLongLnK);
+  const bool u8 = G == 1 && (!LN || RT <= cus || p.K > kLongLnK);
   return u8 ? launch_mfma_k<T, 8, 1, LN>(p, B, G, s) : launch_mfma_k<T, 4, 1, LN>(p, B, G, s);
 }
 
@@ -1968,12 +1986,13 @@ hipError_t launch_gemv_mfma(GemvParams p, int dtype, int B, hipStream_t stream) 
   if (p.ln && (!p.ln_in || p.K > kMaxLnK)) return hipErrorInvalidValue;
   if (p.ln_out && p.y_f32) return hipErrorInvalidValue;
   if (p.ldx < p.K || ((long long)(B - 1) * p.ldx + p.K) * 2 >= (long long)kXPast) return hipErrorInvalidValue;
-  const int G = mfma_splits(p.rows, p.K);
-  if (G > 1 && (!p.ws || !p.cnt || p.ws_floats < mfma_ws_floats(p.rows, p.K, B) ||
-                p.cnt_words < mfma_cnt_words(p.rows, p.K)))
+  const int cus = device_cus(), G = splits_on(p.rows, p.K, cus);
+  const size_t RT = (size_t)((p.rows + kTileRows - 1) / kTileRows);
+  if (G > 1 && (!p.ws || !p.cnt || p.ws_floats < RT * G * kTileRows * B || p.cnt_words < RT))
     return hipErrorInvalidValue;
-  if (p.ln) return dtype == 1 ? launch_mfma_t<BF16, true>(p, B, G, stream) : launch_mfma_t<F16, true>(p, B, G, stream);
-  return dtype == 1 ? launch_mfma_t<BF16, false>(p, B, G, stream) : launch_mfma_t<F16, false>(p, B, G, stream);
+  if (p.ln) return dtype == 1 ? launch_mfma_t<BF16, true>(p, B, G, cus, stream)
+                                : launch_mfma_t<F16, true>(p, B, G, cus, stream);
+  return dtype == 1 ? launch_mfma_t<BF16, false>(p, B, G, cus, stream) : launch_mfma_t<F16, false>(p, B, G, cus, stream);
 }
 
 template <class T, int H>
