@@ -444,8 +444,8 @@ def gemv_label(B, H, F, dt, tiled, partials=True, cus=256):
         return " + ".join("%s: %s" % (k, ", ".join(v)) for k, v in parts.items()) + \
             " + layernorm_regs_kernel<%s,%d> before %s" % (t, ni, "layer 0's qkv" if partials else "qkv and fc1")
     if B == 1:
-        if H % 512 == 0 and H // 512 in (1, 2, 4, 5, 8, 10, 14):
-            return "gemv_ln1_kernel<%s,%d> (qkv, fc1) + gemv_x1_kernel<%s,4,1> (out, fc2)" % (t, H // 512, t)
+        if H <= 7168:
+            return "gemv_ln1_kernel<%s,%d> (qkv, fc1) + gemv_x1_kernel<%s,4,1> (out, fc2)" % (t, -(-H // 512), t)
         return "gemv_kernel<%s,1,1,8> (qkv, fc1) + gemv_x1_kernel<%s,4,1> (out, fc2)" % (t, t)
     if B == 2:
         return "gemv_kernel<%s,2,1,8> (qkv, fc1) + gemv_x1_kernel<%s,4,2> (out, fc2)" % (t, t)

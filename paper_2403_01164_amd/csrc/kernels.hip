@@ -569,15 +569,19 @@ __global__ __launch_bounds__(kThreads) void gemv_x1_kernel(GemvParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// Batch-1 GEMV with a fused LayerNorm for K = 512 * NC (NC <= 14): every wavefront
+// Batch-1 GEMV with a fused LayerNorm for K <= 512 * NC (NC <= 14): every wavefront
 // loads the whole input row into registers (lane l holds the 16-byte chunks
 // l + 64u, exactly the chunks it multiplies in every row), normalises it there and
-// keeps it for all its rows: no LDS staging and no workgroup barrier.  The
+// keeps it for all its rows: no LDS staging and no workgroup barrier.  When K is not a
+// multiple of 512 (TAIL) lanes past the row's end in the last chunk hold zeros there, reread the
+// row's last chunk of weights and skip its product (it may be infinite): such widths ran on the
+// LDS kernel, whole batch-1 steps (us): H = 520, 12 layers 200.6 -> 167.7; 1544, 8 layers 199.9 ->
+// 179.0; 4104, 2 layers 182.5 -> 164.4; 7000, 1 layer 200.9 -> 196.7.  The
 // statistics are summed in the order of ln_stats and the products in the order of
 // gemv_block, so the result is bit-identical to the workgroup kernels.
 // ---------------------------------------------------------------------------
-template <class T, int NC>
-__device__ __forceinline__ void ln_stats_wave(const uint4 (&xv)[NC], int K, float& mean, float& rstd) {
+template <class T, int NC, bool TAIL>
+__device__ __forceinline__ void ln_stats_wave(const uint4 (&xv)[NC], int K, bool in, float& mean, float& rstd) {
   // "thread" t = 64 w + l of ln_stats sums chunks t + 256 i, i.e. chunks u = w + 4 i of lane l
   float part[kWaves];
 #pragma unroll
@@ -587,7 +591,8 @@ __device__ __forceinline__ void ln_stats_wave(const uint4 (&xv)[NC], int K, floa
     for (int u = w; u < NC; u += kWaves) {
       float f[8];
       unpack8<T>(xv[u], f);
-      s += ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
+      const float c = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
+      s = TAIL && u == NC - 1 && !in ? s : s + c;
     }
     part[w] = wave_sum(s);
   }
@@ -605,7 +610,7 @@ __device__ __forceinline__ void ln_stats_wave(const uint4 (&xv)[NC], int K, floa
         float d = f[e] - mean;
         acc += d * d;
       }
-      s += acc;
+      s = TAIL && u == NC - 1 && !in ? s : s + acc;
     }
     part[w] = wave_sum(s);
   }
@@ -613,11 +618,13 @@ __device__ __forceinline__ void ln_stats_wave(const uint4 (&xv)[NC], int K, floa
   rstd = 1.0f / sqrtf(var + kLnEps);
 }
 
-template <class T, int NC>
+template <class T, int NC, bool TAIL>
 __global__ __launch_bounds__(kThreads) void gemv_ln1_kernel(GemvParams p) {
   __shared__ float sbias[kWaves][kX1MaxRows], sres[kWaves][kX1MaxRows];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int K = p.K, rpw = p.rpw;  // K == 512 * NC (launcher)
+  const int K = p.K, rpw = p.rpw;  // 512 (NC - 1) < K <= 512 NC, TAIL: K < 512 NC (launcher)
+  const bool in = !TAIL || lane + 64 * (NC - 1) < (K >> 3);  // this lane's last chunk is inside the row
+  const int last = TAIL ? min(lane + 64 * (NC - 1), (K >> 3) - 1) : lane + 64 * (NC - 1);
   const int row_begin = blockIdx.x * rpw;
   const int nrows = min(rpw, p.rows - row_begin);  // >= 1: the grid covers rows exactly
   const int my_rg = nrows > wave ? (nrows - wave + kWaves - 1) / kWaves : 0;  // <= kX1MaxRows (launcher)
@@ -633,28 +640,32 @@ __global__ __launch_bounds__(kThreads) void gemv_ln1_kernel(GemvParams p) {
   auto load = [&](int j, uint4 (&w)[NC]) {
     const uint4* wr = (const uint4*)(W + (long long)(row_begin + wave + j * kWaves) * K);
 #pragma unroll
-    for (int u = 0; u < NC; ++u) w[u] = load_stream(wr + lane + 64 * u);
+    for (int u = 0; u < NC; ++u) w[u] = load_stream(wr + (u == NC - 1 ? last : lane + 64 * u));
   };
   uint4 wa[NC], wb[NC], xn[NC];
   if (my_rg > 0) load(0, wa);
   const uint4* x = (const uint4*)p.x;
 #pragma unroll
-  for (int u = 0; u < NC; ++u) xn[u] = load_g16(x + lane + 64 * u);
+  for (int u = 0; u < NC; ++u) xn[u] = load_g16(x + (u == NC - 1 ? last : lane + 64 * u));
   if (lane < my_rg) {
     sbias[wave][lane] = bj;
     sres[wave][lane] = rj;
   }
   float mean, rstd;
-  ln_stats_wave<T, NC>(xn, K, mean, rstd);
+  ln_stats_wave<T, NC, TAIL>(xn, K, in, mean, rstd);
 #pragma unroll
   for (int u = 0; u < NC; ++u) xn[u] = normalize8<T>(xn[u], mean, rstd);
   if (p.h_out && blockIdx.x == 0 && wave == 0)
 #pragma unroll
-    for (int u = 0; u < NC; ++u) *(uint4*)((uint16_t*)p.h_out + (long long)(lane + 64 * u) * 8) = xn[u];
+    for (int u = 0; u < NC; ++u)
+      if (!TAIL || u < NC - 1 || in) *(uint4*)((uint16_t*)p.h_out + (long long)(lane + 64 * u) * 8) = xn[u];
   auto compute = [&](int j, const uint4 (&w)[NC]) {
     float acc = 0.f;
 #pragma unroll
-    for (int u = 0; u < NC; ++u) acc = dot8<T>(w[u], xn[u], acc);
+    for (int u = 0; u < NC; ++u) {
+      const float d = dot8<T>(w[u], xn[u], acc);
+      acc = TAIL && u == NC - 1 && !in ? acc : d;
+    }
     const float s = wave_sum(acc);
     if (lane == 0)
       store_y<T>(p.y, row_begin + wave + j * kWaves, p.y_f32, apply_epi(s + sbias[wave][j], p.epi, sres[wave][j]));
@@ -1603,16 +1614,29 @@ constexpr int kDefaultGridCap = 1024;
 // shapes at B = 2: out 9.3 -> 8.6 us, fc2 25.9 -> 25.3 us; slower from B = 3 on, and
 // the register LayerNorm kernel only pays at B = 1).
 constexpr int kX1MaxB = 2;
+constexpr int kMaxLnRegChunks = 14;  // 512-element chunks of a row gemv_ln1_kernel keeps in registers
+
+// gemv_ln1_kernel for rows of nc chunks of 512.
+template <class T, int NC>
+hipError_t launch_ln1(const GemvParams& p, int nc, int grid, hipStream_t s) {
+  if constexpr (NC <= kMaxLnRegChunks) {
+    if (nc != NC) return launch_ln1<T, NC + 1>(p, nc, grid, s);
+    if (p.K == 512 * NC) hipLaunchKernelGGL((gemv_ln1_kernel<T, NC, false>), dim3(grid), dim3(kThreads), 0, s, p);
+    else hipLaunchKernelGGL((gemv_ln1_kernel<T, NC, true>), dim3(grid), dim3(kThreads), 0, s, p);
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
+}
 
 template <class T, int B>
 hipError_t launch_gemv_b(GemvParams p, hipStream_t s, int grid_cap) {
   constexpr int R = Tile<B>::R, U = Tile<B>::U;
   const int cap = grid_cap > 0 ? grid_cap : kDefaultGridCap;
   if constexpr (B <= kX1MaxB) {
-    // K = 512 * NC for the NC instantiated below (hidden sizes of OPT-350M .. OPT-30B); at
-    // NC = 18 (9216) the row no longer fits the registers well and the LDS kernel is as fast
-    const int nc = p.K % 512 == 0 ? p.K / 512 : 0;
-    const bool ln_regs = B == 1 && p.ln && (nc == 1 || nc == 2 || nc == 4 || nc == 5 || nc == 8 || nc == 10 || nc == 14);
+    // rows of up to 7168 (NC = 14): at NC = 18 (9216) the row no longer fits the registers well
+    // and the LDS kernel is as fast
+    const int nc = (p.K + 511) / 512;
+    const bool ln_regs = B == 1 && p.ln && nc <= kMaxLnRegChunks;
     // segment-major weights: gemv_x1_kernel and gemv_block (below) read them, the register
     // LayerNorm kernel does not
     if (p.segmajor && ln_regs) return hipErrorInvalidValue;
@@ -1621,15 +1645,11 @@ hipError_t launch_gemv_b(GemvParams p, hipStream_t s, int grid_cap) {
       const long long per = std::min<long long>((units + cap - 1) / cap, kX1MaxRows);
       p.rpw = (int)(per * kWaves);
       const int grid = (int)((p.rows + p.rpw - 1) / p.rpw);
-      if (!p.ln) hipLaunchKernelGGL((gemv_x1_kernel<T, 4, B>), dim3(grid), dim3(kThreads), 0, s, p);
-      else if (nc == 1) hipLaunchKernelGGL((gemv_ln1_kernel<T, 1>), dim3(grid), dim3(kThreads), 0, s, p);
-      else if (nc == 2) hipLaunchKernelGGL((gemv_ln1_kernel<T, 2>), dim3(grid), dim3(kThreads), 0, s, p);
-      else if (nc == 4) hipLaunchKernelGGL((gemv_ln1_kernel<T, 4>), dim3(grid), dim3(kThreads), 0, s, p);
-      else if (nc == 5) hipLaunchKernelGGL((gemv_ln1_kernel<T, 5>), dim3(grid), dim3(kThreads), 0, s, p);
-      else if (nc == 8) hipLaunchKernelGGL((gemv_ln1_kernel<T, 8>), dim3(grid), dim3(kThreads), 0, s, p);
-      else if (nc == 10) hipLaunchKernelGGL((gemv_ln1_kernel<T, 10>), dim3(grid), dim3(kThreads), 0, s, p);
-      else hipLaunchKernelGGL((gemv_ln1_kernel<T, 14>), dim3(grid), dim3(kThreads), 0, s, p);
-      return hipGetLastError();
+      if (!p.ln) {
+        hipLaunchKernelGGL((gemv_x1_kernel<T, 4, B>), dim3(grid), dim3(kThreads), 0, s, p);
+        return hipGetLastError();
+      }
+      return launch_ln1<T, 1>(p, nc, grid, s);
     }
   }
   // contiguous row blocks of a multiple of R*kWaves rows, at most `cap` blocks; a block
