@@ -65,17 +65,18 @@ constexpr int kMaxBatch = 8;
 // Models created for batches of kTiledMinBatch or more keep their resident rows in the
 // matrix-core tile order and run every batch of kTiledMinBatch or more on the matrix-core GEMV:
 // the vector GEMV's dot products and reads of x grow with the batch (OPT-6.7B-shaped
-// steps: 2.44 / 2.74 / 3.95 ms at batch 2 / 3 / 8 against 2.32 / 2.33 / 2.42 ms on the
-// matrix cores), while at batch 1 the vector kernels with their fused LayerNorm are
-// faster (2.19 against 2.30 ms); with both copies, batch 1 runs the row-major one.
+// steps: 2.44 / 2.74 / 3.95 ms at batch 2 / 3 / 8; on the matrix cores 2.23 ms at batch 8, and
+// 2.32 / 2.33 / 2.42 before the x fragments were shared), while at batch 1 the vector kernels
+// with their fused LayerNorm are faster (2.19 against 2.30 ms then); with both copies, batch 1
+// runs the row-major one.
 constexpr int kTiledMinBatch = 2;
 // Largest hidden size at which the matrix-core qkv and fc1 normalise their input from the
 // LayerNorm partials of the linear before them: their prologue combines H / 16 partials per
-// batch row before the first product, and above this a LayerNorm launch is cheaper (16-layer
-// steps at batch 8 / 3: OPT-13B, H = 5120, 1.961 / 1.763 ms with partials against 2.029 /
-// 1.820 with launches; OPT-30B, 7168, 3.557 / 3.137 against 3.529 / 3.174; OPT-66B, 9216,
-// 5.727 / 5.113 against 5.584 / 5.115).  The choice depends on H alone, so that a batch row's
-// bits do not depend on the batch size.
+// batch row before the first product, and above this a LayerNorm launch was cheaper (16-layer
+// steps at batch 8 / 3, with one row tile per workgroup: OPT-13B, H = 5120, 1.961 / 1.763 ms
+// with partials against 2.029 / 1.820 with launches; OPT-30B, 7168, 3.557 / 3.137 against
+// 3.529 / 3.174; OPT-66B, 9216, 5.727 / 5.113 against 5.584 / 5.115).  The choice depends on H
+// alone, so that a batch row's bits do not depend on the batch size.
 constexpr int kMaxPartialsH = 6144;
 // Largest hidden size at which a model created for batches of 2 or more keeps a row-major
 // copy beside its tiles for batch 1: above it batch 1 is faster on the tiles (all linears
