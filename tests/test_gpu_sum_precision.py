@@ -1,0 +1,45 @@
+"""GPU tests of how the matrix-core GEMVs sum over K: short rows bit for bit as the tree of their
+k-tiles' products that the kernel documents, longer ones by their error against 64-bit sums."""
+import numpy as np
+import pytest
+
+import synth
+from common import np_from_dev, torch_dev_from_np
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+hg = pytest.importorskip("paper_2403_01164_amd")
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = hg.hetegen_create(0)
+    yield c
+    hg.hetegen_destroy(c)
+
+
+def _tiled(ctx, x, W, dtype):
+    (B, K), N = x.shape, W.shape[0]
+    s = torch.cuda.current_stream().cuda_stream
+    xd, Wd = torch_dev_from_np(x), torch_dev_from_np(W)
+    Wt = torch.empty((hg.hetegen_tiled_bytes(N, K) // 2,), dtype=torch.int16, device="cuda")
+    hg.hetegen_tile_weights(ctx, Wd.data_ptr(), N, K, Wt.data_ptr(), s)
+    y = torch.full((B, N), float("nan"), dtype=torch.float32, device="cuda")
+    hg.hetegen_linear_tiled(ctx, xd.data_ptr(), B, K, Wt.data_ptr(), N, dtype, 0, y.data_ptr(), hg.F32, s)
+    torch.cuda.synchronize()
+    return np_from_dev(y, np.float32)
+
+
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+@pytest.mark.parametrize("K", [40, 72, 128, 136, 256])
+def test_short_rows_add_their_tiles_pairwise(ctx, dtype, K):
+    # up to 8 k-tiles no product continues another's sum: the tiles' sums (one-tile calls) are
+    # added two by two.  The order is the kernel's own, so the bits are the same.
+    N, B = 300, 8
+    W, x = synth.normal((N, K), dtype, 0, 81, 0, 0.02), synth.normal((B, K), dtype, 0, 82)
+    t = [_tiled(ctx, np.ascontiguousarray(x[:, k:k + 32]), np.ascontiguousarray(W[:, k:k + 32]), dtype)
+         for k in range(0, K, 32)]
+    t += [np.zeros((B, N), np.float32)] * (8 - len(t))
+    want = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]))
+    assert np.array_equal(_tiled(ctx, x, W, dtype), want)
