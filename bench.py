@@ -370,23 +370,23 @@ def table2_linear(args, torch, synth, hg):
 def mfma_splits(rows, K, cus):
     """Splits of the sum over K in the matrix-core GEMV on a device of `cus` compute units
     (the library's rule: unsplit below 128 k-tiles, or unless one workgroup per 16-row tile
-    loads the units more than 1.15x unevenly, 1.3x below 256 k-tiles; then the fewest splits of
-    at least 32 k-tiles that load them within 1.15x, or the most even)."""
+    loads the units more than 1.15x unevenly; then the fewest splits of at least 32 k-tiles that
+    load them within 1.15x, or the most even, but not 2 below 256 k-tiles up to 1.3x)."""
     def uneven(wgs):
         return -(-wgs // cus) * cus / wgs
     rt, kt = -(-rows // 16), -(-K // 32)
     best, best_u = 1, uneven(rt)
-    if best_u <= 1.15 or kt < 128 or (kt < 256 and best_u <= 1.3):
+    if best_u <= 1.15 or kt < 128:
         return 1
-    g = 2
+    alone, g = best_u, 2
     while g <= 8 and kt // g >= 32:
         u = uneven(rt * g)
-        if u <= 1.15:
-            return g
         if u < best_u:
             best, best_u = g, u
+        if u <= 1.15:
+            break
         g *= 2
-    return best
+    return 1 if kt < 256 and best == 2 and alone <= 1.3 else best
 
 
 def ln_partials_on(H):

@@ -159,11 +159,11 @@ HETEGEN_API hetegen_status hetegen_tile_weights(hetegen_ctx* ctx, const void* W_
  * and N) as in hetegen_linear; bias_dev optional device [N].  Binary32 sums (the
  * matrix core's products of 16-bit values are exact).  When one workgroup per 16-row
  * tile would load the device's compute units unevenly (the busiest more than 1.15x
- * the mean, 1.3x for K <= 8160) and K > 4064, the sum over K is split over up to 8
- * workgroups (each at least 32 32-column tiles long) whose partial sums are added in a
- * fixed order: the split
- * depends on N, K and the device's compute-unit count, not on B or timing, so a
- * batch row's bits do not depend on the batch size.  Uses the context's split-K
+ * the mean) and K > 4064, the sum over K is split over up to 8 workgroups (each at
+ * least 32 32-column tiles long; not over 2 when K <= 8160 and the busiest has at most
+ * 1.3x the mean) whose partial sums are added in a fixed order: the split depends on
+ * N, K and the device's compute-unit count, not on B or timing, so a batch row's bits
+ * do not depend on the batch size.  Uses the context's split-K
  * workspace, which the first call with a larger need allocates (device memory,
  * after waiting for the device); calls on one context must not overlap.  Enqueued
  * on `stream`.  B in [1, 8], K % 8 == 0, N >= 1, B * K < 2^30 (x is read through

@@ -1912,15 +1912,19 @@ static int even_splits(int rows, int K, int cus) {
 // (partial store, arrival, loads) costs about 1.5 us at the tail.  Rows of fewer than 4096
 // columns are not split ([2048, 2048] 4.8 us unsplit against 5.7 in 2, [768, 3072] 4.8 / 5.6,
 // [10240, 2560] with the LayerNorm 11.4 / 13.6, all at B = 2 or 4), rows of fewer than 8192
-// only above 1.3x ([13000, 4360] with the LayerNorm 21.5 us unsplit against 24.8 in 2,
-// [10007, 5128] 18.9 / 20.4; [5120, 5120], 1.6x, takes 4).  Long rows by evenness: OPT-13B fc2
+// not in 2 up to 1.3x ([13000, 4360] with the LayerNorm 21.5 us unsplit against 24.8 in 2,
+// [10007, 5128] 18.9 / 20.4; [5120, 5120], 1.6x, takes 4).  The two accumulators of an unsplit
+// sum keep the error against 64 bits of two splits (0.98-1.00 of it), but not that of four
+// ([6400, 4096] unsplit 1.31, [6400, 8160] 1.39 of it, though 10.4 against 12.7 us at B = 2):
+// those are split as evenness says.  Long rows by evenness: OPT-13B fc2
 // [5120, 20480] (320 row tiles) took 49.4 us unsplit and 39.1 in 4 splits, OPT-6.7B fc2 [4096,
 // 16384] (256 row tiles, even) 23.9 unsplit and 26.2 in 4.  The choice does not depend on B, so
 // a batch row's bits do not either.
 static int splits_on(int rows, int K, int cus) {
   const int KT = (K + kTileK - 1) / kTileK, RT = (rows + kTileRows - 1) / kTileRows;
-  if (KT < kMinTilesToSplit || (KT < kLongTiles && uneven(RT, cus) <= kMaxUnevenShort)) return 1;
-  return even_splits(rows, K, cus);
+  if (KT < kMinTilesToSplit) return 1;
+  const int G = even_splits(rows, K, cus);
+  return KT < kLongTiles && G == 2 && uneven(RT, cus) <= kMaxUnevenShort ? 1 : G;
 }
 
 int mfma_splits(int rows, int K) { return rows <= 0 || K <= 0 ? 1 : splits_on(rows, K, device_cus()); }

@@ -55,7 +55,11 @@ def test_kernel_labels_follow_the_measured_rules():
               (15360, 5120): 1, (5120, 5120): 4, (20480, 5120): 1, (5120, 20480): 4,      # OPT-13B
               (21504, 7168): 1, (7168, 7168): 1, (28672, 7168): 1, (7168, 28672): 1,      # OPT-30B
               (27648, 9216): 1, (9216, 9216): 2, (36864, 9216): 1, (9216, 36864): 2,      # OPT-66B
-              (16400, 36864): 2, (4112, 36864): 8, (256, 1024): 1, (37, 72): 1}
+              (16400, 36864): 2, (4112, 36864): 8, (256, 1024): 1, (37, 72): 1,
+              # both sides of the rule's lines: 128 and 256 k-tiles, 1.3x uneven (630 / 626 row
+              # tiles 1.22 / 1.23, 576 1.33), 2 or more splits below 256 k-tiles
+              (1000, 4064): 1, (1000, 4072): 4, (10007, 8160): 1, (10007, 8168): 2, (9216, 8160): 2,
+              (6400, 4072): 4, (6400, 8160): 4, (2550, 10248): 8, (10007, 5128): 1}
     for (n, k), g in splits.items():
         assert bench.mfma_splits(n, k, 256) == g, (n, k)
     env = os.environ.pop("HETEGEN_LN_PARTIALS", None)

@@ -3,6 +3,7 @@ k-tiles' products that the kernel documents, longer ones by their error against 
 import numpy as np
 import pytest
 
+import bench
 import synth
 from common import np_from_dev, torch_dev_from_np
 
@@ -43,3 +44,16 @@ def test_short_rows_add_their_tiles_pairwise(ctx, dtype, K):
     t += [np.zeros((B, N), np.float32)] * (8 - len(t))
     want = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]))
     assert np.array_equal(_tiled(ctx, x, W, dtype), want)
+
+
+@pytest.mark.parametrize("K", [4104, 8160])
+def test_rows_of_an_uneven_grid_keep_their_four_splits(ctx, K):
+    # 400 row tiles load 256 compute units 1.28x unevenly and take 4 splits, as the same rows do in
+    # a linear of 63 row tiles: the same partial sums, added in the same order.  (Unsplit, their
+    # error against 64 bits is 1.3-1.4 times as large.)
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the shapes are chosen for a 256-CU device")
+    assert bench.mfma_splits(6400, K, 256) == bench.mfma_splits(1000, K, 256) == 4
+    W, x = synth.normal((6400, K), synth.F16, 0, 83, 0, 0.02), synth.normal((8, K), synth.F16, 0, 84)
+    assert np.array_equal(_tiled(ctx, x, W, synth.F16)[:, :1000],
+                          _tiled(ctx, x, np.ascontiguousarray(W[:1000]), synth.F16))
