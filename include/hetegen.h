@@ -180,8 +180,7 @@ HETEGEN_API hetegen_status hetegen_linear_tiled(hetegen_ctx* ctx, const void* x_
  * hetegen_create and held until the process ends (262144 floats of partials and
  * 65536 counters, 1.25 MiB per GPU).  The call allocates nothing; it returns
  * UNSUPPORTED, without launching, for a shape whose split (see hetegen_linear_tiled)
- * would need more than that, i.e. ceil(N / 16) * splits * 16 * B floats with the splits that
- * an even load (1.15x) would take at any K.  On a 256-CU
+ * needs more than that, i.e. ceil(N / 16) * splits * 16 * B floats.  On a 256-CU
  * device every linear of OPT-6.7B to OPT-175B fits at batch 8 (the largest need,
  * OPT-13B's [5120, 5120] and [5120, 20480] in 4 splits, is 163840 floats); a split
  * linear of more than 1024 row tiles at batch 8, such as [16400, 36864], does not.  Every

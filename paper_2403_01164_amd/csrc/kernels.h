@@ -138,8 +138,7 @@ hipError_t launch_tile(const void* W, long long ldw, int rows, int K, void* dst,
 
 // K-splits of the matrix-core GEMV for `rows` rows and reduction length K on the current
 // device (1 = no split; it depends on the device's compute-unit count, not on the batch),
-// and the workspace for a launch at batch B, sized for the most splits an even grid would take
-// (0 when that is one).
+// and the workspace a launch at batch B needs (0 when not split).
 int mfma_splits(int rows, int K);
 // Tile order for a model's copy of W [rows, K] on the current device: 1 k-major, 0 row-tile
 // order (1 when the launch grid puts the same number of workgroups, at most 3, on every CU).

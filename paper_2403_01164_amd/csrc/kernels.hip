@@ -1889,8 +1889,7 @@ static double uneven(long long wgs, int cus) {
 
 // The most K-splits a linear takes, by evenness alone: one workgroup per row tile unless that
 // loads the CUs unevenly (more than 1.15x the mean on the busiest); then the fewest splits
-// that do not, each at least 32 k-tiles long, or else the most even split.  Workspaces are
-// sized by it.
+// that do not, each at least 32 k-tiles long, or else the most even split.
 static int even_splits(int rows, int K, int cus) {
   if (rows <= 0 || K <= 0) return 1;
   const int KT = (K + kTileK - 1) / kTileK, RT = (rows + kTileRows - 1) / kTileRows;
@@ -1945,13 +1944,13 @@ int mfma_kmajor(int rows, int K) {
 }
 
 size_t mfma_ws_floats(int rows, int K, int B) {
-  const int G = even_splits(rows, K, device_cus());
-  if (G == 1 || rows <= 0) return 0;
+  const int G = mfma_splits(rows, K);
+  if (G == 1) return 0;
   return (size_t)((rows + kTileRows - 1) / kTileRows) * G * kTileRows * B;
 }
 
 size_t mfma_cnt_words(int rows, int K) {
-  if (rows <= 0 || even_splits(rows, K, device_cus()) == 1) return 0;
+  if (mfma_splits(rows, K) == 1) return 0;
   return (size_t)((rows + kTileRows - 1) / kTileRows);
 }
 

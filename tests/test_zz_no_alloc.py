@@ -85,3 +85,16 @@ def test_noalloc_refuses_shapes_beyond_its_scratch(ctx):
     rc, y = _status(ctx, 16400, 36864, 4)
     assert rc == hg.OK
     assert np.all(np_from_dev(y, np.float32) == 0.0)
+
+
+@pytest.mark.parametrize("K", [2048, 4096])
+def test_noalloc_runs_uneven_shapes_that_are_not_split(ctx, K):
+    # 1025 row tiles load 256 compute units 1.25x unevenly, and 2 splits would need 262400 partial
+    # floats at batch 8; at these lengths the sum is not split and needs no scratch
+    c = _case(ctx, 16400, K, 8, synth.F16, 130)
+    ref_lib = _call(ctx, c, hg.hetegen_linear_tiled)
+    got = _call(ctx, c, hg.hetegen_linear_tiled_noalloc)
+    assert np.array_equal(got.view(np.uint32), ref_lib.view(np.uint32))
+    rows = np.concatenate([np.arange(64), np.arange(16400 - 64, 16400)])
+    ref = oracle.linear(c["x"], np.ascontiguousarray(c["W"][rows]), c["b"][rows], synth.F16).astype(np.float64)
+    assert rel_err(got[:, rows], ref) <= TOL
