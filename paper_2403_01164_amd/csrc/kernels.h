@@ -95,9 +95,9 @@ hipError_t launch_step(const StepArgs& a, int dtype, int B, int grid, size_t lds
 hipError_t launch_gemv(GemvParams p, int dtype, int B, hipStream_t stream, int grid_cap);
 
 // y = epi(x W^T + bias) with W row-major (no LayerNorm) on the matrix cores, B <= 8; a row's
-// bits depend on rows and K, not on B.  gemv_rows_wanted: whether it is faster than launch_gemv
-// and can run (x within its buffer descriptor).
-bool gemv_rows_wanted(int rows, int K, long long ldx, int B);
+// bits depend on rows and K, not on B.  gemv_rows_wanted: whether it is faster than launch_gemv,
+// no less precise, and can run (x within its buffer descriptor).
+bool gemv_rows_wanted(int rows, int K, long long ldx, int B, int dtype);
 hipError_t launch_gemv_rows(GemvParams p, int dtype, int B, hipStream_t stream);
 
 // Segment-major layout of a row-major weight [rows, K] (K a multiple of kSegElems): the

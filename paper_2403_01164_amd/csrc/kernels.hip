@@ -69,6 +69,7 @@ __device__ __forceinline__ uint4 load_stream(const uint4* p) {
 }
 
 struct F16 {
+  static constexpr bool kRowsTree = false;  // gemv_rows_kernel
   static __device__ __forceinline__ float dot2(uint32_t w, uint32_t x, float acc) {
     return __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, w), __builtin_bit_cast(f16x2, x), acc, false);
   }
@@ -83,6 +84,7 @@ struct F16 {
 };
 
 struct BF16 {
+  static constexpr bool kRowsTree = true;
   static __device__ __forceinline__ float dot2(uint32_t w, uint32_t x, float acc) {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), __builtin_bit_cast(bf16x2, x), acc,
                                            false);
@@ -1195,25 +1197,32 @@ __global__ __launch_bounds__(kThreads) void gemv_rows_kernel(GemvParams p, int B
       f.x[u] = make_uint4(v.x, v.y, v.z, v.w);
     }
   };
-  // A wavefront's sum over K in two levels: chains of 4 products, then the sums of two steps.
-  // In one chain its rounding error against 64 bits was 1.7 times the vector GEMV's (64 lanes'
-  // partials) at K = 5128
+  // A wavefront's sum over K is kept within the vector GEMV's error against 64 bits (64 lanes'
+  // partials) at every K.  binary16: chains of 4 products, then the sums of two steps (in one chain
+  // the error was 1.7 times the vector GEMV's at K = 5128; now 0.37-1.00 of it).  bfloat16, whose
+  // exact products are shorter, so that the vector GEMV rounds less: every product starts from
+  // zero, a step's are added pairwise and the steps in turn (0.86-1.00; with the chains it was
+  // 1.02-1.09 for K = 264..4096).
   constexpr int NH = H == 16 ? 2 : 1;  // the k-tiles of a pair: two products, or one for both
   constexpr int NA = NP / 2;           // accumulators per product
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
   f32x4 acc[NH][NA], sum[NH];
   auto clear = [&] {
 #pragma unroll
     for (int h = 0; h < NH; ++h)
 #pragma unroll
-      for (int n = 0; n < NA; ++n) acc[h][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int n = 0; n < NA; ++n) acc[h][n] = zero;
   };
-  auto fold = [&] {
+  auto fold = [&] {  // what compute has left in acc
+    if constexpr (!T::kRowsTree) {
 #pragma unroll
-    for (int h = 0; h < NH; ++h) sum[h] += NA == 4 ? (acc[h][0] + acc[h][1]) + (acc[h][2 % NA] + acc[h][3 % NA])
-                                                   : acc[h][0] + acc[h][1];
+      for (int h = 0; h < NH; ++h) sum[h] += NA == 4 ? (acc[h][0] + acc[h][1]) + (acc[h][2 % NA] + acc[h][3 % NA])
+                                                     : acc[h][0] + acc[h][1];
+      clear();
+    }
   };
 #pragma unroll
-  for (int h = 0; h < NH; ++h) sum[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int h = 0; h < NH; ++h) sum[h] = zero;
   clear();
   char* my = tile[wave];
   auto compute = [&](int st, const Buf& f) {
@@ -1229,11 +1238,24 @@ __global__ __launch_bounds__(kThreads) void gemv_rows_kernel(GemvParams p, int B
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     const char* op = my + (lane & (H - 1)) * kRow + grp * 16 + (H == 8 ? half * PAIR * 64 : 0);
+    auto weights = [&](int u, int h) { return *(const uint4*)(op + (first(u) + h) * 64); };
+    if constexpr (T::kRowsTree) {
 #pragma unroll
-    for (int u = 0; u < NP; ++u) {
-      acc[0][u % NA] = Mma<T>::run(*(const uint4*)(op + first(u) * 64), f.x[u], acc[0][u % NA]);
-      if constexpr (H == 16)
-        acc[NH - 1][u % NA] = Mma<T>::run(*(const uint4*)(op + first(u) * 64 + 64), f.x[u], acc[NH - 1][u % NA]);
+      for (int h = 0; h < NH; ++h) {
+        f32x4 pr[NP];
+#pragma unroll
+        for (int u = 0; u < NP; ++u) pr[u] = Mma<T>::run(weights(u, h), f.x[u], zero);
+#pragma unroll
+        for (int n = NP / 2; n >= 1; n /= 2)
+#pragma unroll
+          for (int u = 0; u < n; ++u) pr[u] += pr[u + n];
+        sum[h] += pr[0];
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < NP; ++u)
+#pragma unroll
+        for (int h = 0; h < NH; ++h) acc[h][u % NA] = Mma<T>::run(weights(u, h), f.x[u], acc[h][u % NA]);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -1257,7 +1279,6 @@ __global__ __launch_bounds__(kThreads) void gemv_rows_kernel(GemvParams p, int B
     fence();
     compute(st + 1, fb);
     fold();
-    clear();
     fence();
   }
   if (st + 1 < nst) {
@@ -1285,7 +1306,7 @@ __global__ __launch_bounds__(kThreads) void gemv_rows_kernel(GemvParams p, int B
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) s[w] = part[w][0][v][l0] + part[w][H == 16 ? 1 : 0][v][l1];
     store_y<T>(p.y, j * p.ldy + row0 + i, p.y_f32,
-               apply_epi(((s[0] + s[1]) + (s[2] + s[3])) + T::to_f32(bias_v), p.epi, T::to_f32(resid_v)));
+               apply_epi(((s[0] + s[3]) + (s[1] + s[2])) + T::to_f32(bias_v), p.epi, T::to_f32(resid_v)));
   }
 }
 
@@ -2039,8 +2060,12 @@ hipError_t launch_rows_k(const GemvParams& p, int B, hipStream_t s) {
 // up to 1024 rows from B = 3 ([1000, 4096] 4.2 / 4.4 at B = 2, 5.3 / 4.7 at 4, 9.0 / 5.3 at
 // 8), up to 512 long rows from B = 5 ([100, 16384] 9.2 / 9.6 at B = 4, 17.5 / 9.8 at 5).  An x too
 // large for its buffer descriptor stays on the vector GEMV.
-bool gemv_rows_wanted(int rows, int K, long long ldx, int B) {
+bool gemv_rows_wanted(int rows, int K, long long ldx, int B, int dtype) {
   if (B < 1 || B > kLnSlots || ((long long)(B - 1) * ldx + K) * 2 >= (long long)kXPast) return false;
+  // bfloat16 rows a little longer than 2 or 3 steps of 256 columns: the last step's wavefront adds
+  // one more rounding at the size of the result than the vector GEMV has (error against 64 bits
+  // 1.02-1.00 of it for K = 520..584, 1.01-1.00 for 776..832; every other K 0.86-1.00)
+  if (dtype == 1 && K > 512 && K < 1024 && K % 256 > 0 && K % 256 < 96) return false;
   if (rows <= kRowsFew / 2 && K > kRowsLongK) return B >= 5;
   if (rows <= kRowsFew) return B >= 3;
   return B >= 2 || rows > kRowsMany;

@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 import bench
+import oracle
 import synth
 from common import np_from_dev, torch_dev_from_np
 
@@ -57,3 +58,31 @@ def test_rows_of_an_uneven_grid_keep_their_four_splits(ctx, K):
     W, x = synth.normal((6400, K), synth.F16, 0, 83, 0, 0.02), synth.normal((8, K), synth.F16, 0, 84)
     assert np.array_equal(_tiled(ctx, x, W, synth.F16)[:, :1000],
                           _tiled(ctx, x, np.ascontiguousarray(W[:1000]), synth.F16))
+
+
+def _rows(ctx, x, W, dtype):
+    (B, K), N = x.shape, W.shape[0]
+    xd, Wd = torch_dev_from_np(x), torch_dev_from_np(W)
+    y = torch.full((B, N), float("nan"), dtype=torch.float32, device="cuda")
+    hg.hetegen_linear(ctx, xd.data_ptr(), B, K, Wd.data_ptr(), Wd.data_ptr(), N, dtype, 0, 0, 0.0, y.data_ptr(), hg.F32,
+                      torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    return np_from_dev(y, np.float32)
+
+
+# 16 rows per workgroup but for the 1000-row shape (8); K: one step of 256 or 512 columns and a little
+# more, the middle of a step, several steps
+@pytest.mark.parametrize("dtype,N,K", [(synth.BF16, 4096, 264), (synth.BF16, 4096, 520), (synth.BF16, 4096, 784),
+                                       (synth.BF16, 1000, 1032), (synth.BF16, 4096, 1544), (synth.BF16, 4096, 2056),
+                                       (synth.BF16, 4096, 4096), (synth.F16, 4096, 520), (synth.F16, 1000, 1032)])
+def test_row_major_rows_are_as_precise_at_batch_8_as_alone(ctx, dtype, N, K):
+    # batch 8 sums on the matrix cores (where that is no less precise), a single batch row of as few
+    # rows on the vector GEMV.  The two errors are taken over 8 N = 8000 .. 32768 outputs; 1.02 leaves
+    # room for the sampling error of their ratio (below 0.8 %), 1.02-1.09 being what chained products
+    # gave bfloat16 at these lengths.
+    W, x = synth.normal((N, K), dtype, 0, 85, 0, 0.02), synth.normal((8, K), dtype, 0, 86)
+    ref = oracle.decode(x, dtype).astype(np.float64) @ oracle.decode(W, dtype).astype(np.float64).T
+    together = _rows(ctx, x, W, dtype)
+    alone = np.concatenate([_rows(ctx, np.ascontiguousarray(x[b:b + 1]), W, dtype) for b in range(8)])
+    e = [np.sqrt(np.mean((y.astype(np.float64) - ref) ** 2)) for y in (together, alone)]
+    assert e[0] <= 1.02 * e[1], e[0] / e[1]
