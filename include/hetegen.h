@@ -123,6 +123,11 @@ HETEGEN_API hetegen_status hetegen_host_free(hetegen_ctx* ctx, void* p);
  *   bias_dev       optional device [N] w_dtype, read for the GPU rows.  Pass both
  *                  or neither (a side with rows needs its pointer).
  *   y_dev          device [B, N] of y_dtype (w_dtype or HETEGEN_F32), row stride N.
+ * Binary32 sums.  Resident GPU rows are summed by the matrix cores or the vector
+ * units, whichever suits N, K, w_dtype and B, and the two add in different orders: the
+ * last bits of a row of y may differ between batch sizes, between resident and streamed
+ * rows and between a row on the GPU and on the host; they do not depend on alpha while
+ * the row stays on the GPU, on timing, or on the other batch rows' values.
  * GPU work is enqueued on `stream`.  The call returns after the CPU share is
  * computed and its upload is enqueued; y is complete in `stream` order.
  * B in [1, 8], K % 8 == 0, K >= 8, N >= 1.  NOT_PINNED if W_host is pageable and

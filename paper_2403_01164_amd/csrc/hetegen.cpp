@@ -658,8 +658,8 @@ hetegen_status run_gemv(hetegen_ctx* ctx, const Job& j, const void* x, long long
     p.ln_in = ln ? j.ln_in : nullptr;
     p.ln_out = j.ln_out;
     HIPCHK(ctx, hg::launch_gemv_mfma(p, j.dtype, j.B, st));
-  } else if (resident && j.rows_mfma && hg::gemv_rows_wanted(rows, j.K, ldx, j.B, j.dtype)) {
-    HIPCHK(ctx, hg::launch_gemv_rows(p, j.dtype, j.B, st));
+  } else if (resident && j.rows_mfma && hg::gemv_rows_wanted(j.N, j.K, ldx, j.B, j.dtype)) {
+    HIPCHK(ctx, hg::launch_gemv_rows(p, j.N, j.dtype, j.B, st));
   } else {
     HIPCHK(ctx, hg::launch_gemv(p, j.dtype, j.B, st, 0));
   }

@@ -94,11 +94,12 @@ hipError_t launch_step(const StepArgs& a, int dtype, int B, int grid, size_t lds
 // (0 = default).  Returns the launch status.
 hipError_t launch_gemv(GemvParams p, int dtype, int B, hipStream_t stream, int grid_cap);
 
-// y = epi(x W^T + bias) with W row-major (no LayerNorm) on the matrix cores, B <= 8; a row's
-// bits depend on rows and K, not on B.  gemv_rows_wanted: whether it is faster than launch_gemv,
-// no less precise, and can run (x within its buffer descriptor).
-bool gemv_rows_wanted(int rows, int K, long long ldx, int B, int dtype);
-hipError_t launch_gemv_rows(GemvParams p, int dtype, int B, hipStream_t stream);
+// y = epi(x W^T + bias) with W row-major (no LayerNorm) on the matrix cores, B <= 8; the p.rows
+// rows belong to a linear of N, and a row's bits depend on N and K, not on B or p.rows.
+// gemv_rows_wanted: whether that linear is faster so than by launch_gemv, no less precise, and
+// can run (x within its buffer descriptor).  launch_gemv adds in another order.
+bool gemv_rows_wanted(int N, int K, long long ldx, int B, int dtype);
+hipError_t launch_gemv_rows(GemvParams p, int N, int dtype, int B, hipStream_t stream);
 
 // Segment-major layout of a row-major weight [rows, K] (K a multiple of kSegElems): the
 // kSegElems-element segment s of row r is stored at (s * rows + r) * kSegElems elements, so

@@ -779,8 +779,9 @@ constexpr int kMaxKmajorPerCu = 3;  // mfma_kmajor
 constexpr int kLongSplitTiles = 128;  // mfma_rows
 // gemv_rows_wanted, rows_by_8
 constexpr int kRowsFew = 1024, kRowsMany = 16384;
-constexpr int kRowsMinK8 = 1024, kRowsLongK = 8192;
-constexpr double kRowsUneven = 1.2;
+constexpr int kRowsMinK8 = 1024, kRowsLongK = 3584;
+constexpr double kRowsUneven = 1.2, kRowsLopsided = 1.4;
+constexpr long long kLdsPerCu = 160 * 1024;
 constexpr int kLongLnK = 4096;        // launch_mfma_t
 constexpr int kLnGroup = 16;    // elements per LayerNorm partial
 constexpr int kLnSlots = 8;     // batch rows per partial group (the largest batch)
@@ -2050,45 +2051,74 @@ hipError_t launch_rows_k(const GemvParams& p, int B, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Resident row-major rows on the matrix cores: from B = 2 on, where the vector GEMV is bound
-// by its products and its reads of x (us, vector / matrix cores, B = 2, 4 and 8: [16384, 4096]
-// 26.2 / 23.6, 24.8 / 23.9, 31.5 / 24.9; [10007, 5128] 27.5 / 19.7, 22.3 / 20.1, 35.2 / 23.7;
-// [4096, 4096] 9.1 / 8.1, 9.9 / 8.4, 12.7 / 8.6; [2560, 10240] 13.8 / 13.2, 14.9 / 12.9, 21.2 /
-// 14.4; [32000, 264] 17.3 / 9.8, 13.6 / 9.8, 18.7 / 10.4), and at B = 1 for many rows, which
-// there are several to a wavefront ([36864, 9216] 111.1 / 97.9, [20480, 5120] 35.8 / 33.3, but
-// [16384, 4096] 22.1 / 23.8).  Few rows leave CUs idle sooner than with one row per wavefront:
-// up to 1024 rows from B = 3 ([1000, 4096] 4.2 / 4.4 at B = 2, 5.3 / 4.7 at 4, 9.0 / 5.3 at
-// 8), up to 512 long rows from B = 5 ([100, 16384] 9.2 / 9.6 at B = 4, 17.5 / 9.8 at 5).  An x too
-// large for its buffer descriptor stays on the vector GEMV.
-bool gemv_rows_wanted(int rows, int K, long long ldx, int B, int dtype) {
+// Row strides (2 K bytes) at which the rows of a workgroup crowd a few memory channels: 16 and
+// 32 KiB, and (skewed) 64 bytes off a multiple of 16 KiB or 32 bytes off an odd multiple of 8 KiB.
+static bool rows_skewed(int K) {
+  const int m = K % 8192;
+  return K > 4000 && (m == 32 || m == 8192 - 32 || m == 4096 - 16 || m == 4096 + 16);
+}
+static bool rows_crowded(int K) { return K == 8192 || K == 16384 || rows_skewed(K); }
+
+// Resident row-major rows of a linear [N, K] on the matrix cores (N, not the GPU's share of it, so
+// that a GPU row's bits do not depend on alpha).  The vector GEMV is bound by its products and by
+// its reads of x from LDS, the more the larger the batch and again where x (2 B K bytes) lets one
+// workgroup on a CU or does not fit; the matrix cores by an uneven grid and crowded channels.  The
+// lines lie where both are equal in a sweep of 24 row counts (64..40000) by 44 lengths (64..36864);
+// speed over it against the vector GEMV, geometric mean and worst: B = 1 1.01 / 0.98, 2 1.18 / 0.93,
+// 3 1.09 / 0.92, 4 1.14 / 0.92, 5 1.30 / 0.94, 6 1.36 / 0.95, 8 1.45 / 0.93.  us, vector / matrix cores:
+//  * B = 1: only with several rows to a wavefront, [18000, 264] 8.7 / 6.4, [20480, 5128] 36.5 /
+//    34.8, [36864, 9216] 111 / 98; not K = 1032..2048 nor strides of 4 to 32 KiB, [20480, 2048]
+//    14.6 / 17.2, [20480, 8192] 52.6 / 53.5.
+//  * up to 1024 rows CUs are idle that one row per wavefront keeps busy: [1000, 4096] 4.0 / 4.4 at
+//    B = 2, 4.8 / 4.6 at 3, 9.0 / 5.4 at 8; [1000, 8208] 6.8 / 7.2 at 3.
+//  * crowded channels: [12288, 8160] 39.3 / 43.1 at 4, 56.7 / 47.2 at 8; [4096, 16384] 26.0 / 29.1 at
+//    2, 29.4 / 29.6 at 4; [12288, 2048] 10.8 / 12.2 at 3, 12.2 / 11.9 at 4.
+//  * B = 3, where the vector GEMV is at its best: [5120, 12288] 23.3 / 24.4, [12288, 12288] 49.0 /
+//    46.7, [4200, 5128] 12.4 / 11.8; beyond the LDS [1500, 28672] 27.1 / 18.0.
+//  * B = 4, uneven grids: [4200, 8064] 15.7 / 17.1, [4200, 5128] 13.2 / 12.5.
+//  * B = 8, x beyond the LDS: [16400, 16000] (uneven) 95.8 / 105.8, [12288, 16000] 72.1 / 63.7.
+// An x too large for its buffer descriptor stays on the vector GEMV.
+bool gemv_rows_wanted(int N, int K, long long ldx, int B, int dtype) {
   if (B < 1 || B > kLnSlots || ((long long)(B - 1) * ldx + K) * 2 >= (long long)kXPast) return false;
   // bfloat16 rows a little longer than 2 or 3 steps of 256 columns: the last step's wavefront adds
   // one more rounding at the size of the result than the vector GEMV has (error against 64 bits
   // 1.02-1.00 of it for K = 520..584, 1.01-1.00 for 776..832; every other K 0.86-1.00)
   if (dtype == 1 && K > 512 && K < 1024 && K % 256 > 0 && K % 256 < 96) return false;
-  if (rows <= kRowsFew / 2 && K > kRowsLongK) return B >= 5;
-  if (rows <= kRowsFew) return B >= 3;
-  return B >= 2 || rows > kRowsMany;
+  const int n16 = (N + 15) / 16, cus = device_cus();
+  const double grid = n16 > cus ? uneven(n16, cus) : 1.0;
+  const long long x_bytes = 2LL * B * K;
+  if (B == 1) {
+    for (int p = 2048; p <= 16384; p *= 2)
+      if (abs(K - p) <= p / 64) return false;
+    return N > kRowsMany && (K <= 1024 || K > 2048);
+  }
+  if (B <= 4 && rows_skewed(K)) return false;
+  if (B <= 4 && N <= kRowsFew) return B >= 3 && (K <= (B == 3 ? 4096 : 6144) || x_bytes > kLdsPerCu);
+  if (B == 2) return N > 4096 || abs(K - 16384) > 128;
+  if (B == 3) return N <= 4096 || x_bytes > kLdsPerCu || (abs(K - 2048) > 32 && K <= (grid <= kRowsLopsided ? 9216 : 3072));
+  if (B == 4) return grid <= kRowsLopsided || K <= 6144 || x_bytes > kLdsPerCu / 2;
+  return B <= 6 || grid <= kRowsUneven || x_bytes < kLdsPerCu;
 }
 
 // Rows per workgroup: 8 (twice the workgroups, x read as often as W) when 16 would leave more
-// than half of the CUs idle, load them unevenly, or leave one or two workgroups per CU on long
-// rows; 16 otherwise and on rows too short for four wavefronts of 512 columns (us, 8 / 16
-// rows, B = 4: [1000, 4096] 4.7 / 5.6, [10007, 5128] 20.0 / 21.2, [6000, 6000] 14.6 / 16.1,
-// [4096, 16384] 27.6 / 29.3; [20480, 5120] 35.5 / 31.7, [8192, 2048] 9.1 / 8.4, [32000, 264]
-// 15.7 / 9.8).
-static bool rows_by_8(int rows, int K) {
-  const int n16 = (rows + 15) / 16, cus = device_cus();
+// than half of the CUs idle or load them unevenly, and on crowded channels (half as many rows at
+// a time, twice as much of each); 16 otherwise and on rows too short for that.  us, 8 / 16 rows:
+// [1000, 4096] 4.8 / 5.8 at B = 4; [10007, 5128] 19.4 / 20.6 at 2, 23.9 / 23.8 at 8; [6000, 6144] 14.2 /
+// 15.7, 17.6 / 18.1; [4096, 16384] 29.1 / 32.5, 31.0 / 32.0; [12288, 8160] 42.4 / 49.4, 47.2 / 53.5; but
+// [20480, 5128] 37.8 / 36.2 at 4, [8192, 2048] 9.1 / 8.3, [28672, 264] 13.5 / 8.6.
+static bool rows_by_8(int N, int K) {
+  const int n16 = (N + 15) / 16, cus = device_cus();
   if (K < kRowsMinK8) return false;
-  return n16 <= cus / 2 || (n16 > cus && uneven(n16, cus) > kRowsUneven) ||
-         (K >= kRowsLongK && n16 % cus == 0 && n16 <= 2 * cus);
+  if (n16 <= cus / 2) return true;
+  if (rows_crowded(K) && (n16 > cus || uneven((N + 7) / 8, cus) <= kRowsLopsided)) return true;
+  return K >= kRowsLongK && n16 > cus && uneven(n16, cus) > kRowsUneven;
 }
 
-hipError_t launch_gemv_rows(GemvParams p, int dtype, int B, hipStream_t stream) {
+hipError_t launch_gemv_rows(GemvParams p, int N, int dtype, int B, hipStream_t stream) {
   if (p.rows <= 0) return hipSuccess;
   if (p.K < 8 || p.K % 8 || B < 1 || B > kLnSlots || p.ln || p.segmajor) return hipErrorInvalidValue;
   if (p.ldx < p.K || ((long long)(B - 1) * p.ldx + p.K) * 2 >= (long long)kXPast) return hipErrorInvalidValue;
-  if (rows_by_8(p.rows, p.K))
+  if (rows_by_8(N, p.K))
     return dtype == 1 ? launch_rows_k<BF16, 8>(p, B, stream) : launch_rows_k<F16, 8>(p, B, stream);
   return dtype == 1 ? launch_rows_k<BF16, 16>(p, B, stream) : launch_rows_k<F16, 16>(p, B, stream);
 }
