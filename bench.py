@@ -401,16 +401,19 @@ def mfma_rows(rows, K, g, ln, cus):
     """Row tiles per workgroup of the matrix-core GEMV (the library's rule)."""
     rt, kt = -(-rows // 16), -(-K // 32)
     load = lambda r: -(-(-(-rt // r) * g) // cus) * r
-    even = rt * g % cus == 0
+    u = load(1) * cus / (rt * g)
     if g > 1:
-        if even and not ln and kt // g < 128 and 5 * load(3) <= 6 * load(1):
+        if u <= 1.05 and not ln and kt // g < 128 and 5 * load(3) <= 6 * load(1):
             return 3
-        return 5 if load(5) <= load(1) and (ln or not even or kt // g >= 128) else 1
-    if even and not ln:
-        return 2 if rt % (2 * cus) == 0 and rt <= 4 * cus else 1
-    if load(3) <= min(load(1), load(2)):
+        return 5 if load(5) <= load(1) and (ln or u > 1.05 or kt // g >= 128) else 1
+    if not ln and kt <= 20:
+        return 1 if rt <= cus else 3 if load(3) <= load(2) else 2
+    if not ln and 28 < kt <= (40 if rt > 4 * cus else 32):
+        return 1
+    if load(3) <= min(load(1), load(2)) and (ln or u > 1.1):
         return 3
-    return 2 if load(2) <= load(1) else 1
+    many_even = not ln and rt > 4 * cus and u <= 1.05
+    return 2 if load(2) <= load(1) and not (many_even and kt > 64) else 1
 
 
 def gemv_label(B, H, F, dt, tiled, partials=True, cus=256):

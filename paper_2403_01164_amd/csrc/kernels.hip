@@ -776,7 +776,10 @@ constexpr int kMinTilesToSplit = 128, kLongTiles = 256;  // k-tiles of a row
 constexpr double kMaxUnevenShort = 1.3;                   // below kLongTiles
 constexpr int kMaxDevices = 64, kDefaultCus = 256;
 constexpr int kMaxKmajorPerCu = 3;  // mfma_kmajor
-constexpr int kLongSplitTiles = 128;  // mfma_rows
+// mfma_rows
+constexpr int kLongSplitTiles = 128;
+constexpr double kRowTilesEven = 1.05, kRowTilesUneven = 1.1;
+constexpr int kSoonTiles = 20, kFullTiles = 32, kFullTilesMany = 40, kShortRowTiles = 64;  // k-tiles of a row
 // gemv_rows_wanted, rows_by_8
 constexpr int kRowsFew = 1024, kRowsMany = 16384;
 constexpr int kRowsMinK8 = 1024, kRowsLongK = 3584;
@@ -1979,29 +1982,38 @@ size_t mfma_cnt_words(int rows, int K) {
 // Row tiles per workgroup.  More of them share the x fragments (and the LayerNorm prologue
 // and normalisation) of a k-tile, but make the grid coarser: what a CU then reads is
 // ceil(workgroups / CUs) * R row tiles, and R is taken only where that is no more than with
-// one row tile per workgroup.  Unsplit: the largest such R up to 3; where one row tile per
-// workgroup already loads the CUs evenly and there is no LayerNorm, only 2 for grids of 2
-// or 4 per CU ([8192, 4096] 15.1 -> 12.5 us, [16384, 4096] 23.2 -> 22.9; none of 3, 6 or 8).
-// Split: 5 on an uneven grid, with the LayerNorm or for long splits (it brings the OPT-66B
-// grids, 1152 workgroups, to 232, all running at once), 3 for short splits of an even grid up
-// to a fifth more per CU (the workgroups of an even grid in row-tile order walk K in step and
-// crowd a few memory channels), else 1.  Measured at B = 8 (us, R = 1 / 2 / 3 / 5): [15360,
-// 5120] with the LayerNorm 29.0 / 27.0 / 33.6 / 30.1, [16384, 4096] with it 25.2 / 23.5 / 27.8
-// / 25.0, [7168, 28672] 70.2 / 65.2 / 79.4 / 115, [21504, 7168] 51.7 / 51.0 / 50.2 / 70.5,
-// [28672, 7168] 64.1 / 67.8 / 72.3 / 79.7; split [9216, 36864] in 2 115 / 120 / 120 / 105,
-// [5120, 20480] in 4 39.6 / 39.8 / 38.8 / 38.2, [5120, 5120] in 4 14.0 / 15.6 / 13.2 / 14.5,
-// [2560, 10240] in 8 14.5 / 15.5 / 13.5 / 14.6.  R does not change the bits.
+// one row tile per workgroup.
+//  * Unsplit with the LayerNorm: the largest such R up to 3.  B = 8 (us, R = 1 / 2 / 3 / 5): [15360,
+//    5120] 29.0 / 27.0 / 33.6 / 30.1, [16384, 4096] 25.2 / 23.5 / 27.8 / 25.0.
+//  * Unsplit without: 2, or 3 on a grid that one row tile per workgroup loads more than 1.1x
+//    unevenly (R = 1 / 2 / 3: [5120, 3072] 9.0 / 8.0 / 10.0, [14336, 4096] 21.1 / 20.3 / 26.0, [8300,
+//    3072], 1.48x, 12.5 / 13.9 / 11.3, but [12272, 3072], 1.001x, 13.5 / 14.8 / 14.4).  Rows of up to
+//    640 columns are over so soon that fewer workgroups win on every grid above one per CU
+//    ([16384, 264] 6.0 / 4.2 / 5.0, [20480, 520] 7.5 / 7.0 / 6.7).  Rows of 904 to 1024 are one full
+//    request of 8 k-tiles per wavefront, which only R = 1 makes; above 4 row tiles per CU it wins up
+//    to 1280 ([40000, 1024] at B = 1 14.2 / 15.7 / 15.9, [24576, 1152] at 8 11.5 / 12.6 / 11.3), and on
+//    an even grid of so many from 2056 on too ([24576, 4096] at B = 4 31.0 / 32.5, but 1536 14.4 / 13.4).
+//  * Split: 5 on an uneven grid, with the LayerNorm or for long splits (it brings the OPT-66B
+//    grids, 1152 workgroups, to 232, all running at once), 3 for short splits of an even grid up
+//    to a fifth more per CU (the workgroups of an even grid in row-tile order walk K in step and
+//    crowd a few memory channels), else 1.  B = 8, R = 1 / 3 / 5: [9216, 36864] in 2 115 / 120 / 105,
+//    [5120, 20480] in 4 39.6 / 38.8 / 38.2, [5120, 5120] in 4 14.0 / 13.2 / 14.5 and [5056, 5120],
+//    1.01x, the same, [2560, 10240] in 8 14.5 / 13.5 / 14.6; [8300, 4096] in 4, 1.11x, 16.7 / 18.4 / 20.1.
+// R does not change the bits.
 static int mfma_rows(int rows, int K, int G, bool ln, int cus) {
   const int KT = (K + kTileK - 1) / kTileK, RT = (rows + kTileRows - 1) / kTileRows;
   auto load = [&](int r) { return ((long long)(RT + r - 1) / r * G + cus - 1) / cus * r; };
-  const bool even = (long long)RT * G % cus == 0;
+  const double u = uneven((long long)RT * G, cus);
   if (G > 1) {
+    const bool even = u <= kRowTilesEven;
     if (even && !ln && KT / G < kLongSplitTiles && 5 * load(3) <= 6 * load(1)) return 3;
     return load(5) <= load(1) && (ln || !even || KT / G >= kLongSplitTiles) ? 5 : 1;
   }
-  if (even && !ln) return RT % (2 * cus) == 0 && RT <= 4 * cus ? 2 : 1;
-  if (load(3) <= std::min(load(1), load(2))) return 3;
-  return load(2) <= load(1) ? 2 : 1;
+  if (!ln && KT <= kSoonTiles) return RT <= cus ? 1 : load(3) <= load(2) ? 3 : 2;
+  if (!ln && KT > kFullTiles - kChunkTiles && KT <= (RT > 4 * cus ? kFullTilesMany : kFullTiles)) return 1;
+  if (load(3) <= std::min(load(1), load(2)) && (ln || u > kRowTilesUneven)) return 3;
+  const bool many_even = !ln && RT > 4 * cus && u <= kRowTilesEven;
+  return load(2) <= load(1) && !(many_even && KT > kShortRowTiles) ? 2 : 1;
 }
 
 template <class T, int U, int R, bool LN>

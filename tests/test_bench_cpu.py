@@ -62,6 +62,21 @@ def test_kernel_labels_follow_the_measured_rules():
               (6400, 4072): 4, (6400, 8160): 4, (2550, 10248): 8, (10007, 5128): 1}
     for (n, k), g in splits.items():
         assert bench.mfma_splits(n, k, 256) == g, (n, k)
+    # row tiles per workgroup, without and with the LayerNorm prologue (on 256 CUs; both sides of
+    # each line, and the shapes the tests of the kernel's row-tile groups rely on)
+    rows = {(5999, 40): 2, (5999, 552): 2, (8192, 72): 2, (11985, 296): 3, (4096, 640): 1, (4112, 640): 2,
+            (20480, 640): 3, (20480, 648): 1, (4112, 896): 2, (4112, 904): 1, (4112, 1024): 1, (4112, 1032): 2,
+            (24576, 1280): 1, (24576, 1288): 2, (16384, 1288): 2, (24576, 2048): 2, (24576, 2056): 1,
+            (9190, 1056): 3, (9216, 2048): 3, (10007, 2088): 3, (11152, 2048): 3, (11184, 2048): 1, (12288, 2048): 1,
+            (15360, 5120): 2, (16384, 4096): 2, (8192, 4096): 2, (12288, 4096): 1, (28672, 7168): 1,
+            (9190, 4136): 5, (2550, 10248): 3, (5120, 5120): 3, (5056, 5120): 3, (5136, 5120): 1, (5120, 20480): 5,
+            (9216, 36864): 5, (8300, 4096): 1, (1000, 4104): 1}
+    for (n, k), r in rows.items():
+        assert bench.mfma_rows(n, k, bench.mfma_splits(n, k, 256), False, 256) == r, (n, k)
+    with_ln = {(12288, 4096): 3, (16384, 4096): 2, (15360, 5120): 2, (20480, 5120): 1, (6000, 2000): 2, (11984, 2000): 3,
+               (9192, 4136): 5}
+    for (n, k), r in with_ln.items():
+        assert bench.mfma_rows(n, k, bench.mfma_splits(n, k, 256), True, 256) == r, (n, k)
     env = os.environ.pop("HETEGEN_LN_PARTIALS", None)
     try:
         assert bench.ln_partials_on(4096) and bench.ln_partials_on(5120)

@@ -23,11 +23,11 @@ def ctx():
     hg.hetegen_destroy(c)
 
 
-# rows -> row tiles per workgroup on 256 CUs: 5999 (375 tiles) 2, 11985 (750) 3, 8192 (512) 2,
-# 9190 (575, K split 2) 5, 2550 (160, K split 4) 3; K: odd numbers of k-tiles, partial chunks
-# of 4, K % 32 != 0
+# row tiles per workgroup on 256 CUs: 2 for the first three and 6991 rows, 3 for 11985 (750 tiles) of
+# 296, 9190 (575) and 10007 (626) unsplit and 2550 in 8 splits, 5 for 9190 in 2 splits, 1 for 11985 and
+# 12288 (768) rows of 1056; K: odd numbers of k-tiles, partial chunks of 4, K % 32 != 0
 @pytest.mark.parametrize("N,K", [(5999, 40), (5999, 552), (8192, 72), (11985, 296), (11985, 1056), (10007, 2088),
-                                 (9190, 4136), (2550, 10248)])
+                                 (9190, 4136), (2550, 10248), (9190, 1064), (6991, 1096), (12288, 1056)])
 @pytest.mark.parametrize("B", [1, 5, 8])
 def test_row_groups_integer_inputs_bit_exact(ctx, N, K, B):
     # x, W in {-1, 0, 1}, bias in {-4..4}: every partial sum is exact, so any order of the
