@@ -28,10 +28,9 @@ struct AttnParams {
   float scale;  // set by the launcher: log2(e) / sqrt(head_dim)
 };
 
-// Positions per workgroup of the attention kernel for short caches (the smallest chunk:
-// a partial buffer of ceil(max_seq / attn_chunk()) chunks per (batch, head) holds any
-// position's chunks).
-int attn_chunk();
+// Chunks of positions (one workgroup each) of the longest launch for a cache of `positions`: a
+// partial buffer of as many per (batch, head) holds any launch on it.
+int attn_max_chunks(int positions);
 
 // Largest cache (positions) the attention kernel supports.
 int attn_max_positions();

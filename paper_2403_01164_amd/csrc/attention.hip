@@ -32,6 +32,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "attention.h"
 
 namespace hg {
@@ -43,7 +45,8 @@ constexpr int kMidChunk = 128;   // positions per workgroup (512 threads) from k
 constexpr int kMidFrom = 384;
 constexpr int kLongChunk = 256;  // positions per workgroup (512 threads) from kLongFrom positions on
 constexpr int kLongFrom = 2048;
-constexpr int kMaxChunks = 256;  // chunks the merge holds in LDS; kChunk * kMaxChunks: the longest cache
+constexpr int kMaxChunks = 64;   // chunks the merge holds in LDS
+constexpr int kMaxPositions = kMaxChunks * kLongChunk;  // the longest cache
 constexpr int kMergeRegs = 16;   // chunks whose partial outputs the merge requests at once
 
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
@@ -383,15 +386,27 @@ hipError_t launch_kv_copy_d(const KvCopyParams& a, int B, bool to_cache, hipStre
 
 }  // namespace
 
-int attn_chunk() { return kChunk; }
+static int chunk_of(int positions) {
+  return positions >= kLongFrom ? kLongChunk : positions >= kMidFrom ? kMidChunk : kChunk;
+}
+static int chunks_of(int positions) {
+  const int ch = chunk_of(positions);
+  return (positions + ch - 1) / ch;
+}
 
-int attn_max_positions() { return kChunk * kMaxChunks; }
+int attn_max_positions() { return kMaxPositions; }
+
+// the most chunks lie at the end of the cache or just before a larger chunk is taken
+int attn_max_chunks(int positions) {
+  return std::max({chunks_of(positions), chunks_of(std::min(positions, kMidFrom - 1)),
+                   chunks_of(std::min(positions, kLongFrom - 1))});
+}
 
 hipError_t launch_attention(AttnParams a, int dtype, int B, hipStream_t stream) {
   if (B < 1 || a.pos < 0 || a.pos >= a.max_seq || (a.head_dim != 64 && a.head_dim != 128) || a.heads < 1)
     return hipErrorInvalidValue;
-  const int ch = a.pos + 1 >= kLongFrom ? kLongChunk : a.pos + 1 >= kMidFrom ? kMidChunk : kChunk;
-  a.nchunk = (a.pos + ch) / ch;  // chunks covering positions [0, pos]
+  const int ch = chunk_of(a.pos + 1);
+  a.nchunk = chunks_of(a.pos + 1);
   if (a.nchunk > a.max_chunks || a.nchunk > kMaxChunks) return hipErrorInvalidValue;
   a.scale = 1.4426950408889634f / sqrtf((float)a.head_dim);  // log2 e / sqrt(D)
   return dtype == 1 ? launch_ch<BF16>(a, ch, B, stream) : launch_ch<F16>(a, ch, B, stream);

@@ -2503,11 +2503,10 @@ hetegen_status hetegen_model_kv_create(hetegen_ctx* ctx, hetegen_model* m, int m
       return fail(ctx, HETEGEN_ERR_UNSUPPORTED, "head_dim %d: 64 or 128, dividing H = %d", head_dim, m->H);
     if (m->kv) return fail(ctx, HETEGEN_ERR_INVALID_ARG, "kv_create: the model already has a KV cache");
     HIPCHK(ctx, hipSetDevice(ctx->device));
-    const int chunk = hg::attn_chunk();
     m->heads = m->H / head_dim;
     m->head_dim = head_dim;
     m->kv_seq = max_seq;
-    m->kv_chunks = (max_seq + chunk - 1) / chunk;
+    m->kv_chunks = hg::attn_max_chunks(max_seq);
     const size_t kv_bytes = 2 * (size_t)m->L * kv_layer_elems(m) * 2;
     const size_t part_bytes = (size_t)m->max_batch * m->heads * m->kv_chunks * (head_dim + 2) * sizeof(float);
     const size_t cnt_bytes = (size_t)m->max_batch * m->heads * sizeof(uint32_t);

@@ -788,7 +788,6 @@ constexpr long long kLdsPerCu = 160 * 1024;
 constexpr int kLongLnK = 4096;        // launch_mfma_t
 constexpr int kLnGroup = 16;    // elements per LayerNorm partial
 constexpr int kLnSlots = 8;     // batch rows per partial group (the largest batch)
-constexpr int kLnMaxGroups = kMaxLnK / kLnGroup;
 
 // LayerNorm statistics of B rows from their partials (see ln_partials_floats): the mean
 // is the sum of the group sums over K, and the variance combines each group's squared

@@ -46,6 +46,27 @@ def test_chunk_edges(ctx, dtype, head_dim, P):
         m.free()
 
 
+# the last position of caches that end just before and at a larger chunk (6 chunks of 64, 3 of 128; 16 of
+# 128, 8 of 256), and at 16 and 17 chunks of 256, around what the merge requests at once: the partial
+# buffer holds the most chunks of any position of that cache, so earlier ones run too
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("P,earlier", [(63, []), (382, [319]), (383, [382]), (2046, [382]), (2047, [2046]), (2100, [2046]),
+                                       (4095, [2046]), (4096, [2046])])
+def test_full_caches(ctx, head_dim, P, earlier):
+    B, H, dtype = 2, 256, synth.F16
+    m = Model(ctx, 1, H, 512, dtype, 0.0, 1, max_batch=2)
+    try:
+        hg.hetegen_model_kv_create(ctx, m.m, P + 1, head_dim)
+        kc, vc = _fill_cache(m, B, P)
+        x = synth.normal((B, H), dtype, 0, synth.act_id(P))
+        for p in [P] + earlier:
+            out, tr = m.step_kv(x, p, trace=True)
+            last, _ = m.check_teacher_forced(x, tr, attn=_attn_ref(m, [kc[0][:, :p]], [vc[0][:, :p]], head_dim))
+            assert np.array_equal(out, last), p
+    finally:
+        m.free()
+
+
 @pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
 @pytest.mark.parametrize("P,hot", [(60, 17), (400, 131), (2100, 0), (2100, 2099)])
 def test_scores_far_apart(ctx, dtype, P, hot):

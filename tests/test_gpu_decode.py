@@ -634,8 +634,8 @@ def test_kv_opt67b_shape_one_layer_context_512(ctx):
 
 
 def test_kv_largest_cache_last_position(ctx):
-    # the largest cache the header allows (16384 positions), decoding its last position: 256
-    # chunks, all but the first 16 merged through the kernel's tail loop
+    # the largest cache the header allows (16384 positions), decoding its last position: 64
+    # chunks of 256, all but the first 16 merged through the kernel's tail loop
     dtype, L, H, F, B, D, S = synth.F16, 1, 256, 512, 2, 128, 16384
     m = Model(ctx, L, H, F, dtype, 0.0, 1, max_batch=2)
     try:
@@ -689,8 +689,8 @@ def test_kv_argument_errors(ctx):
 
 @pytest.mark.parametrize("P", [1023, 1100, 2046, 2047, 2175])
 def test_kv_long_context_merge(ctx, P):
-    # more chunks than the merge requests at once (16 x 64 positions), and around the
-    # switch to 128-position chunks at 2048 positions (2175: 17 chunks of 128)
+    # 8 to 16 chunks of 128 positions (16 are what the merge requests at once) and the switch to
+    # 256-position chunks at 2048 positions
     dtype, L, H, F, B, D = synth.BF16, 1, 256, 512, 2, 128
     m = Model(ctx, L, H, F, dtype, 0.0, 1)
     try:
