@@ -341,9 +341,10 @@ hipError_t launch_ch(const AttnParams& a, int ch, int B, hipStream_t s) {
 // same values (keys: which = 0, values: 1).  A workgroup moves 4 positions of a group of
 // heads: a head's rows of 4 positions are contiguous in the cache (1 KiB at head_dim 128),
 // a position's rows of the heads are contiguous in the buffer, so both sides move whole
-// lines, kCopyIter 16-byte loads per thread in flight.  Bound by HBM: 512 positions of 8
-// sequences of 32 heads (D = 128) written and read back take 43 us, 6.3 TB/s of reads and
-// writes.
+// lines, kCopyIter 16-byte loads per thread in flight.  Bound by memory: 512 positions of 8
+// sequences of 32 heads (D = 128) written and read back take 43 us (268 MB moved; part of the
+// read comes from the memory-side cache, a plain copy between buffers that do not fit it runs at
+// 4.8 TB/s).
 constexpr int kCopyTok = 4;
 constexpr int kCopyIter = 4;
 

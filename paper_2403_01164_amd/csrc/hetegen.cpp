@@ -2545,21 +2545,25 @@ hetegen_status kv_copy(hetegen_ctx* ctx, hetegen_model* m, int l, int B, int pos
   HIPCHK(ctx, hipSetDevice(ctx->device));
   const size_t per = kv_layer_elems(m), D = m->head_dim, row = D * 2, tok = (size_t)m->H * 2;
   // One kernel moves keys and values of all heads and sequences.  Buffers it cannot read
-  // or write directly (host or managed memory, another device's) or that are not 16-byte
-  // aligned go through one 2-D copy per head, sequence and side, which takes them all but
-  // costs 2.6 us each on the device: 512 positions of 8 sequences of 32 heads, in and out,
-  // 2650 us against 43 us (6.3 TB/s read and written).
+  // or write directly (pinned or managed memory, another device's), that are not 16-byte
+  // aligned or not wholly inside one allocation go through one 2-D copy per head, sequence
+  // and side: the runtime takes or refuses those (it checks each copy against the
+  // allocation, the kernel cannot), at 2.6 us each on the device: 512 positions of 8 sequences
+  // of 32 heads, in and out, 2650 us against 43 us.
+  const size_t bytes = (size_t)B * n * tok;
   auto direct = [&](const void* p) {
     hipPointerAttribute_t at;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
     if (!aligned16(p)) return false;
-    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    if (hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeDevice || at.device != ctx->device ||
+        hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
       (void)hipGetLastError();
       return false;
     }
-    return at.type == hipMemoryTypeDevice && at.device == ctx->device;
+    return (size_t)((const char*)p - (const char*)base) + bytes <= size;
   };
   // (key and value buffers of a read that overlap are written one after the other)
-  const size_t bytes = (size_t)B * n * tok;
   const bool apart = (char*)k + bytes <= (char*)v || (char*)v + bytes <= (char*)k;
   if ((to_cache || apart) && direct(k) && direct(v)) {
     hg::KvCopyParams a{};
