@@ -575,8 +575,8 @@ __global__ __launch_bounds__(kThreads) void gemv_x1_kernel(GemvParams p) {
 // loads the whole input row into registers (lane l holds the 16-byte chunks
 // l + 64u, exactly the chunks it multiplies in every row), normalises it there and
 // keeps it for all its rows: no LDS staging and no workgroup barrier.  When K is not a
-// multiple of 512 (TAIL) lanes past the row's end in the last chunk hold zeros there, reread the
-// row's last chunk of weights and skip its product (it may be infinite): such widths ran on the
+// multiple of 512 (TAIL) lanes past the row's end in the last chunk reread the row's last chunk of
+// the input and of the weights and leave both out of their sums: such widths ran on the
 // LDS kernel, whole batch-1 steps (us): H = 520, 12 layers 200.6 -> 167.7; 1544, 8 layers 199.9 ->
 // 179.0; 4104, 2 layers 182.5 -> 164.4; 7000, 1 layer 200.9 -> 196.7.  The
 // statistics are summed in the order of ln_stats and the products in the order of
@@ -1102,7 +1102,7 @@ __global__ __launch_bounds__(kThreads) void gemv_mfma_kernel(GemvParams p, int B
     __syncthreads();
     if (!last) return;
     // the partials are requested together (one round trip) and added in split order; a split
-    // past G reads past the descriptor's size or another tile's partial and is not added
+    // past G reads past the descriptor's size and is not added
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       float pv[kMaxSplits];
