@@ -2095,14 +2095,14 @@ bool gemv_rows_wanted(int N, int K, long long ldx, int B, int dtype) {
   // one more rounding at the size of the result than the vector GEMV has (error against 64 bits
   // 1.02-1.00 of it for K = 520..584, 1.01-1.00 for 776..832; every other K 0.86-1.00)
   if (dtype == 1 && K > 512 && K < 1024 && K % 256 > 0 && K % 256 < 96) return false;
-  const int n16 = (N + 15) / 16, cus = device_cus();
-  const double grid = n16 > cus ? uneven(n16, cus) : 1.0;
-  const long long x_bytes = 2LL * B * K;
   if (B == 1) {
     for (int p = 2048; p <= 16384; p *= 2)
       if (abs(K - p) <= p / 64) return false;
     return N > kRowsMany && (K <= 1024 || K > 2048);
   }
+  const int n16 = (N + 15) / 16, cus = device_cus();
+  const double grid = n16 > cus ? uneven(n16, cus) : 1.0;
+  const long long x_bytes = 2LL * B * K;
   if (B <= 4 && rows_skewed(K)) return false;
   if (B <= 4 && N <= kRowsFew) return B >= 3 && (K <= (B == 3 ? 4096 : 6144) || x_bytes > kLdsPerCu);
   if (B == 2) return N > 4096 || abs(K - 16384) > 128;
