@@ -2117,9 +2117,13 @@ bool gemv_rows_wanted(int N, int K, long long ldx, int B, int dtype) {
 // [1000, 4096] 4.8 / 5.8 at B = 4; [10007, 5128] 19.4 / 20.6 at 2, 23.9 / 23.8 at 8; [6000, 6144] 14.2 /
 // 15.7, 17.6 / 18.1; [4096, 16384] 29.1 / 32.5, 31.0 / 32.0; [12288, 8160] 42.4 / 49.4, 47.2 / 53.5; but
 // [20480, 5128] 37.8 / 36.2 at 4, [8192, 2048] 9.1 / 8.3, [28672, 264] 13.5 / 8.6.
-static bool rows_by_8(int N, int K) {
+// bfloat16 rows a little longer than 2 or 3 steps of 512 columns take 16: with 8 the last step's
+// wavefront rounds once more at the size of the result (error against 64 bits 1.02 of the vector
+// GEMV's at K = 1032, 1.01 at 1088, 1.004 at 1544; with 16 rows 0.99-1.00).
+static bool rows_by_8(int N, int K, int dtype) {
   const int n16 = (N + 15) / 16, cus = device_cus();
   if (K < kRowsMinK8) return false;
+  if (dtype == 1 && K < 2048 && K % 512 > 0 && K % 512 < 128) return false;
   if (n16 <= cus / 2) return true;
   if (rows_crowded(K) && (n16 > cus || uneven((N + 7) / 8, cus) <= kRowsLopsided)) return true;
   return K >= kRowsLongK && n16 > cus && uneven(n16, cus) > kRowsUneven;
@@ -2129,7 +2133,7 @@ hipError_t launch_gemv_rows(GemvParams p, int N, int dtype, int B, hipStream_t s
   if (p.rows <= 0) return hipSuccess;
   if (p.K < 8 || p.K % 8 || B < 1 || B > kLnSlots || p.ln || p.segmajor) return hipErrorInvalidValue;
   if (p.ldx < p.K || ((long long)(B - 1) * p.ldx + p.K) * 2 >= (long long)kXPast) return hipErrorInvalidValue;
-  if (rows_by_8(N, p.K))
+  if (rows_by_8(N, p.K, dtype))
     return dtype == 1 ? launch_rows_k<BF16, 8>(p, B, stream) : launch_rows_k<F16, 8>(p, B, stream);
   return dtype == 1 ? launch_rows_k<BF16, 16>(p, B, stream) : launch_rows_k<F16, 16>(p, B, stream);
 }

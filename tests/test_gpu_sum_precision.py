@@ -70,10 +70,11 @@ def _rows(ctx, x, W, dtype):
     return np_from_dev(y, np.float32)
 
 
-# 16 rows per workgroup but for the 1000-row shape (8); K: one step of 256 or 512 columns and a little
-# more, the middle of a step, several steps
+# 16 rows per workgroup but for the shapes of up to 2000 rows (8, where that is no less precise: not
+# bfloat16 at 1032); K: one step of 256 or 512 columns and a little more, the middle of a step, several steps
 @pytest.mark.parametrize("dtype,N,K", [(synth.BF16, 4096, 264), (synth.BF16, 4096, 520), (synth.BF16, 4096, 784),
-                                       (synth.BF16, 1000, 1032), (synth.BF16, 4096, 1544), (synth.BF16, 4096, 2056),
+                                       (synth.BF16, 1000, 1032), (synth.BF16, 2000, 1032), (synth.BF16, 2000, 1160),
+                                       (synth.BF16, 2000, 2056), (synth.BF16, 4096, 1544), (synth.BF16, 4096, 2056),
                                        (synth.BF16, 4096, 4096), (synth.F16, 4096, 520), (synth.F16, 1000, 1032)])
 def test_row_major_rows_are_as_precise_at_batch_8_as_alone(ctx, dtype, N, K):
     # batch 8 sums on the matrix cores (where that is no less precise), a single batch row of as few
